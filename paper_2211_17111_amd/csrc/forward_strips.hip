@@ -36,6 +36,7 @@
 
 #include "device_utils.h"
 #include "internal.h"
+#include "strip_args.h"
 #include "vec.h"
 
 #include <algorithm>
@@ -77,37 +78,6 @@ static_assert(kItemPairs % kNT == 0 && kItemPairs % kLoadThreads == 0 &&
 static_assert(kItemPairsBig <= 65536, "segment index fits 16 bits");
 static_assert(2 * buf_bytes(kItemPairsBig) + 16 * 1024 <= 160 * 1024, "two big item buffers fit LDS");
 static_assert(kShareItems <= kHdrCache, "a share's item headers fit the cache");
-
-struct StripArgs {
-  const int32_t* hdr;
-  const int32_t* pair_rd0;
-  const uint32_t* pair_ln;
-  const uint16_t* pair_seg;
-  const int32_t* item_strip;
-  const int32_t* item_pair0;
-  const int32_t* item_seg0;
-  const int32_t* seg_dest;
-  const int32_t* comb_cell;
-  const int32_t* comb_slot0;
-  const int32_t* empty;
-  const int32_t* share_item0;
-  float* slots;
-  int64_t slot_cap;  // slots the workspace holds
-  int32_t n_valid, n_occ, n_slots, items_cap;  // counts the launch was sized from
-  int32_t item_pairs;  // the item size the launch's kernel holds (schedule_item_pairs)
-  const double* lse;  // fused depth softmax: per-pixel log-sum-exp of the logits (else unused)
-  int32_t dhw;       // D * H * W (points of one view)
-  int32_t C, H, W, bh, bw, nhb, nwb, strips;
-  int32_t hw32;    // H * W
-  int64_t P, cells, n_empty;
-};
-
-// The schedule's header must hold the counts the launch was sized from.
-__device__ __forceinline__ bool header_ok(const StripArgs& a) {
-  const int32_t* hdr = a.hdr;
-  return hdr[kHdrOcc] == a.n_occ && hdr[kHdrOccFound] == a.n_occ && hdr[kHdrValid] == a.n_valid &&
-         hdr[kHdrSlots] == a.n_slots && hdr[kHdrItemPairs] == a.item_pairs;
-}
 
 struct PairRec {
   float w;      // summed depth score
@@ -871,7 +841,10 @@ hipError_t run(const Dims& d, const StripDims& sd, const void* depth, const void
   const int64_t per_die_slots = std::max<int64_t>(forward_workgroups() / kXcds,
                                                   a.items_cap / ((int64_t)kXcds * kHdrCache) + 1);
   const int blocks = (int)(per_die_slots * kXcds);
-  if (a.item_pairs == kItemPairsBig)
+  if (VEC > 1 && dense_forward_ok(d, sd, sizeof(TIn) == 2, a.n_valid, a.n_occ, a.n_slots)) {
+    const hipError_t e = launch_forward_dense(d, sd, sizeof(TIn) == 2, sizeof(TOut) == 2, depth, feat, a, out, stream);
+    if (e != hipSuccess) return e;
+  } else if (a.item_pairs == kItemPairsBig)
     k_fwd_strips<TIn, TOut, VEC, SM, kItemPairsBig><<<dim3((unsigned)blocks, chunks), dim3(kNT), 0, stream>>>(
         static_cast<const TIn*>(depth), static_cast<const TIn*>(feat), o, a);
   else
