@@ -8,12 +8,10 @@
 // From the plan alone (bevpool_backward):
 //   1. k_fill + k_point_map scatter the plan back into frustum-index order,
 //      map[p] = BEV rank of p, or -1 when p was dropped;
-//   2. k_backward gives each feature-map pixel to a group of GS lanes (GS a
-//      power of two covering the row's 16-byte vectors).  The group keeps the
-//      pixel's feature row in registers, walks its D depth points, gathers the
-//      upstream-gradient row of each kept point's cell, reduces the dot
-//      product across the group for grad_depth and accumulates
-//      depth * grad_out for grad_feat.
+//   2. k_bwd_pixels (below) with the pairs found on the fly: lane l of a pixel's
+//      group reads depth bin l of the current chunk, consecutive bins of one
+//      cell become a pair, and the pairs move to the group's first lanes.
+//      Dropped points get their zero from the lane that read them.
 //
 // From a schedule (bevpool_backward_scheduled), which lists every pixel's
 // pairs (a cell and a run of consecutive depth bins):
@@ -39,7 +37,6 @@ namespace {
 
 constexpr int kBwdThreads = 256;
 constexpr int kBwdWaves = kBwdThreads / kWave;
-constexpr int kBwdUnroll = 4;
 
 __global__ __launch_bounds__(256) void k_fill(int32_t* __restrict__ map, int64_t n, int32_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -58,128 +55,6 @@ __global__ __launch_bounds__(256) void k_point_map(const int32_t* __restrict__ r
   }
 }
 
-template <typename TIn, typename TG, int VEC, int NV>
-__global__ __launch_bounds__(kBwdThreads) void k_backward(
-    const TG* __restrict__ grad_out, const TIn* __restrict__ depth, const TIn* __restrict__ feat,
-    const int32_t* __restrict__ map, TIn* __restrict__ grad_depth, TIn* __restrict__ grad_feat,
-    int32_t C, int32_t D, int64_t hw, int64_t rows, int GS) {
-  const int lane = lane_id();
-  const int G = kWave / GS;
-  const int g = lane / GS;
-  const int vi = lane - g * GS;
-  const int64_t f = ((int64_t)blockIdx.x * kBwdWaves + threadIdx.x / kWave) * G + g;
-  const bool pix_ok = f < rows;
-  const int CV = C / VEC;
-
-  float fv[NV][VEC];
-  float acc[NV][VEC];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int v = vi + k * GS;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[k][e] = 0.f;
-    if (pix_ok && v < CV) {
-      Vec<TIn, VEC>::load(feat + f * C + (int64_t)v * VEC, fv[k]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) fv[k][e] = 0.f;
-    }
-  }
-
-  const int64_t bn = pix_ok ? f / hw : 0;
-  const int64_t p0 = bn * D * hw + (pix_ok ? f % hw : 0);  // point at depth 0
-
-  for (int d0 = 0; d0 < D; d0 += GS) {
-    // one depth point per lane: cell and depth score, zero grad for drops
-    const int dl = d0 + vi;
-    int my_cell = -1;
-    float my_dep = 0.f;
-    if (pix_ok && dl < D) {
-      const int64_t p = p0 + (int64_t)dl * hw;
-      my_cell = map[p];
-      if (my_cell >= 0) {
-        my_dep = to_float(depth[p]);
-      } else {
-        grad_depth[p] = (TIn)0.f;
-      }
-    }
-    const int nd = min(GS, D - d0);
-    for (int k0 = 0; k0 < nd; k0 += kBwdUnroll) {
-      int cell[kBwdUnroll];
-      float dep[kBwdUnroll];
-      float gv[kBwdUnroll][NV][VEC];
-#pragma unroll
-      for (int u = 0; u < kBwdUnroll; ++u) {
-        const int src = g * GS + ((k0 + u) & (GS - 1));
-        cell[u] = __shfl(my_cell, src);
-        dep[u] = __shfl(my_dep, src);
-        if (k0 + u >= nd) cell[u] = -1;
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-          const int v = vi + k * GS;
-          if (cell[u] >= 0 && v < CV) {
-            Vec<TG, VEC>::load(grad_out + (int64_t)cell[u] * C + (int64_t)v * VEC, gv[u][k]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) gv[u][k][e] = 0.f;
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kBwdUnroll; ++u) {
-        float part = 0.f;
-#pragma unroll
-        for (int k = 0; k < NV; ++k)
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            part = fmaf(gv[u][k][e], fv[k][e], part);
-            acc[k][e] = fmaf(dep[u], gv[u][k][e], acc[k][e]);
-          }
-        for (int o = GS >> 1; o > 0; o >>= 1) part += __shfl_xor(part, o);
-        if (vi == 0 && cell[u] >= 0)
-          grad_depth[p0 + (int64_t)(d0 + k0 + u) * hw] = (TIn)part;
-      }
-    }
-  }
-
-  if (pix_ok) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int v = vi + k * GS;
-      if (v < CV) Vec<TIn, VEC>::store(grad_feat + f * C + (int64_t)v * VEC, acc[k]);
-    }
-  }
-}
-
-template <typename TIn, typename TG, int VEC, int NV>
-hipError_t run(const Dims& d, const void* grad_out, const void* depth, const void* feat,
-               const int32_t* map, void* grad_depth, void* grad_feat, hipStream_t stream) {
-  const int CV = (int)d.C / VEC;
-  const int per_lane = (CV + NV - 1) / NV;
-  int GS = 1;
-  while (GS < per_lane) GS <<= 1;
-  const int G = kWave / GS;
-  const int64_t pix_per_block = (int64_t)G * kBwdWaves;
-  const dim3 grid((unsigned)((d.rows + pix_per_block - 1) / pix_per_block));
-  k_backward<TIn, TG, VEC, NV><<<grid, dim3(kBwdThreads), 0, stream>>>(
-      static_cast<const TG*>(grad_out), static_cast<const TIn*>(depth),
-      static_cast<const TIn*>(feat), map, static_cast<TIn*>(grad_depth),
-      static_cast<TIn*>(grad_feat), (int32_t)d.C, (int32_t)d.D, d.hw, d.rows, GS);
-  return hipGetLastError();
-}
-
-template <typename TIn, typename TG, int VEC>
-hipError_t run_nv(const Dims& d, const void* grad_out, const void* depth, const void* feat,
-                  const int32_t* map, void* grad_depth, void* grad_feat, hipStream_t stream) {
-  const int64_t CV = d.C / VEC;
-  if (CV <= 64) return run<TIn, TG, VEC, 1>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  if (CV <= 128) return run<TIn, TG, VEC, 2>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  if (CV <= 256) return run<TIn, TG, VEC, 4>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  if (CV <= 512) return run<TIn, TG, VEC, 8>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  return run<TIn, TG, VEC, 16>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-}
-
-
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void k_zero_vec(T* __restrict__ a, int64_t nvec) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -187,6 +62,7 @@ __global__ __launch_bounds__(256) void k_zero_vec(T* __restrict__ a, int64_t nve
 }
 
 struct PixArgs {
+  const int32_t* map;  // plan form: BEV rank of every frustum point, -1 for a dropped one
   const int32_t* pix_pair0;
   const int32_t* bp_cell;
   const uint32_t* bp_dn;
@@ -253,7 +129,13 @@ struct ReduceScatter {
 // SIMD (96 VGPRs): float16 rows of 8 channels need 104 and would run 4 (large:
 // 251 -> 230 us, at most 4 registers spilled); wider rows (NV > 1) would spill
 // heavily and are left to the compiler.
-template <typename TIn, typename TG, int VEC, int NV, int GS, int UMAX, int MW>
+//
+// PLAN: the pairs come from a map of the points' cells instead of a schedule,
+// GS depth bins at a time (a run that crosses such a chunk is two pairs).  Where
+// every bin used to be a step of the walk (a pixel at 640x1600 has 118 bins, 58
+// kept points and 41 pairs) and each dot product was reduced for itself: 143 -> 54
+// us there.
+template <typename TIn, typename TG, int VEC, int NV, int GS, int UMAX, int MW, bool PLAN>
 __global__ __launch_bounds__(kBwdThreads)
 __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pixels(
     const TG* __restrict__ grad_out, const TIn* __restrict__ depth, const TIn* __restrict__ feat,
@@ -284,8 +166,8 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
     for (int e = 0; e < VEC; ++e) acc[k][e] = fv[k][e] = 0.f;
     if (v < CV) Vec<TIn, VEC>::load(feat + f * C + (int64_t)v * VEC, fv[k]);
   }
-  const int32_t p_begin = max(a.pix_pair0[f], 0);
-  const int32_t p_end = min(a.pix_pair0[f + 1], a.n_pairs);
+  const int32_t p_begin = PLAN ? 0 : max(a.pix_pair0[f], 0);
+  const int32_t p_end = PLAN ? a.D : min(a.pix_pair0[f + 1], a.n_pairs);  // (depth bins of the plan form)
   const int64_t dbase = (f / a.hw) * a.per_view + f % a.hw;  // depth rank at bin 0
   // (MW > 0) the depth bins this pixel's pairs cover: each lane marks its own
   // pairs' runs; the other bins are dropped points, cleared at the end
@@ -298,7 +180,46 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
     int32_t my_cell = -1;
     uint32_t my_dn = 0;
     float my_w = 0.f;
-    if (pb + vi < p_end) {
+    int cnt = min(GS, p_end - pb);
+    if constexpr (PLAN) {
+      // bin pb + vi: its cell and score; the first of each run of bins of one
+      // cell adds up the run, and sends it to the lane of its number
+      int32_t c = -1;
+      float dep = 0.f;
+      if (pb + vi < p_end) {
+        const int64_t p = dbase + (int64_t)(pb + vi) * a.hw;
+        c = a.map[p];
+        dep = to_float(depth[p]);
+        if (c < 0 || c >= a.cells) {
+          c = -1;
+          grad_depth[p] = (TIn)0.f;
+        }
+      }
+      // continues the run of the bin before (positive scores only: what a
+      // point of another score adds to an infinite gradient does not merge)
+      const int32_t key = dep > 0.f ? c : -1;
+      const int32_t left = __shfl_up(key, 1, GS);
+      const bool same = key >= 0 && vi > 0 && left == key;
+      const bool head = c >= 0 && !same;
+      const uint64_t heads = wave_ballot(head), runs = wave_ballot(same);
+      int n = 1;  // bins of the run that starts here: itself and the continuing bins after it
+      if (lane < kWave - 1) {
+        const uint64_t more = ~(runs >> (lane + 1));
+        n += more != 0 ? (int)__builtin_ctzll(more) : 0;
+      }
+      my_w = dep;
+      for (int j = 1; wave_ballot(head && j < n) != 0; ++j) {
+        const float t = __shfl(dep, min(lane + j, kWave - 1));
+        if (j < n) my_w += t;
+      }
+      const uint64_t group = GS == kWave ? ~0ull : ((1ull << GS) - 1) << (g * GS);
+      cnt = (int)__popcll(heads & group);
+      // (the other lanes send "no cell" to the lanes after the pairs)
+      const int to = 4 * (g * GS + (head ? rank_below(heads & group) : cnt + rank_below(~heads & group)));
+      my_cell = __builtin_amdgcn_ds_permute(to, head ? c : -1);
+      my_dn = (uint32_t)__builtin_amdgcn_ds_permute(to, vi | n << 16);  // (bin within the chunk)
+      my_w = __builtin_bit_cast(float, __builtin_amdgcn_ds_permute(to, __builtin_bit_cast(int, my_w)));
+    } else if (pb + vi < p_end) {
       const int32_t c = a.bp_cell[pb + vi];
       const uint32_t dn = a.bp_dn[pb + vi];
       const int32_t d0 = (int32_t)(dn & 0xffffu), n = (int32_t)(dn >> 16);
@@ -326,7 +247,6 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
         my_w = wsum;
       }
     }
-    const int cnt = min(GS, p_end - pb);
     for (int j0 = 0; j0 < cnt; j0 += U) {
       int32_t cell[U];
       uint32_t dn[U];
@@ -373,7 +293,7 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
         for (int u = 0; u < U; ++u)
           if (u == base + i) c = cell[u], d = dn[u];
         if (c >= 0) {
-          const int32_t d0 = (int32_t)(d & 0xffffu), n = (int32_t)(d >> 16);
+          const int32_t d0 = (PLAN ? pb : 0) + (int32_t)(d & 0xffffu), n = (int32_t)(d >> 16);
           for (int32_t q = vi & (LPU - 1); q < n; q += LPU)
             grad_depth[dbase + (int64_t)(d0 + q) * a.hw] = (TIn)part[i];
         }
@@ -428,6 +348,13 @@ hipError_t run_pixels(const Dims& d, const void* grad_out, const void* depth, co
         static_cast<const TG*>(grad_out), static_cast<const TIn*>(depth),
         static_cast<const TIn*>(feat), static_cast<TIn*>(grad_depth), static_cast<TIn*>(grad_feat), b);
   };
+  if (a.map != nullptr) {  // from the plan alone (dropped points cleared by the kernel)
+    if (many)
+      launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 4, 0, true>);
+    else
+      launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 8, 0, true>);
+    return hipGetLastError();
+  }
   // dropped points: zeros written by the pixel kernel (small launch, D within
   // its bin mask), else by a clearing launch before it
   const bool mask = !many && d.D <= kPixMaskBits;
@@ -436,11 +363,11 @@ hipError_t run_pixels(const Dims& d, const void* grad_out, const void* depth, co
     if (e != hipSuccess) return e;
   }
   if (many)
-    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 4, 0>);
+    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 4, 0, false>);
   else if (mask)
-    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 8, kPixMaskWords>);
+    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 8, kPixMaskWords, false>);
   else
-    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 8, 0>);
+    launch(k_bwd_pixels<TIn, TG, VEC, NV, GS, 8, 0, false>);
   return hipGetLastError();
 }
 
@@ -473,6 +400,30 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 size_t backward_workspace_bytes(const Dims& d) { return sizeof(int32_t) * (size_t)d.P; }
 
+// The pixel kernel for the operands' types, channels and alignment.
+static hipError_t dispatch_pixels(const Dims& d, int in_dtype, int out_dtype, const void* grad_out,
+                                  const void* depth, const void* feat, const PixArgs& a, void* grad_depth,
+                                  void* grad_feat, hipStream_t stream) {
+  const bool al = aligned16(grad_out) && aligned16(feat) && aligned16(grad_feat);
+  if (in_dtype == BEVPOOL_F32) {
+    // 8 channels per lane where C allows: smaller lane groups, so more pixels
+    // (and their independent load chains) per wave
+    if (al && d.C % 8 == 0)
+      return run_pixels_nv<float, float, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+    if (al && d.C % 4 == 0)
+      return run_pixels_nv<float, float, 4>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+    return run_pixels_nv<float, float, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+  }
+  if (out_dtype == BEVPOOL_F16) {
+    if (al && d.C % 8 == 0)
+      return run_pixels_nv<half_t, half_t, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+    return run_pixels_nv<half_t, half_t, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+  }
+  if (al && d.C % 8 == 0)
+    return run_pixels_nv<half_t, float, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+  return run_pixels_nv<half_t, float, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+}
+
 hipError_t launch_backward(const Dims& d, int in_dtype, int out_dtype, const void* grad_out,
                            const void* depth, const void* feat, const int32_t* rd,
                            const int32_t* rb, int32_t n_valid, void* grad_depth,
@@ -484,21 +435,15 @@ hipError_t launch_backward(const Dims& d, int in_dtype, int out_dtype, const voi
         rd, rb, n_valid, map, d.P, d.cells);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-
-  const bool al = aligned16(grad_out) && aligned16(feat) && aligned16(grad_feat);
-  if (in_dtype == BEVPOOL_F32) {
-    if (al && d.C % 4 == 0)
-      return run_nv<float, float, 4>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-    return run_nv<float, float, 1>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  }
-  if (out_dtype == BEVPOOL_F16) {
-    if (al && d.C % 8 == 0)
-      return run_nv<half_t, half_t, 8>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-    return run_nv<half_t, half_t, 1>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  }
-  if (al && d.C % 8 == 0)
-    return run_nv<half_t, float, 8>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
-  return run_nv<half_t, float, 1>(d, grad_out, depth, feat, map, grad_depth, grad_feat, stream);
+  PixArgs a{};
+  a.map = map;
+  a.C = (int32_t)d.C;
+  a.D = (int32_t)d.D;
+  a.hw = (int32_t)d.hw;
+  a.per_view = d.per_view;
+  a.rows = d.rows;
+  a.cells = d.cells;
+  return dispatch_pixels(d, in_dtype, out_dtype, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
 }
 
 
@@ -517,7 +462,7 @@ hipError_t launch_backward_scheduled(const Dims& d, int in_dtype, int out_dtype,
   // (grad_depth's dropped points are cleared by run_pixels)
   const ScheduleLayout L = schedule_layout(d, n_valid, n_intervals);
   const char* sc = static_cast<const char*>(schedule);
-  PixArgs a;
+  PixArgs a{};
   a.pix_pair0 = reinterpret_cast<const int32_t*>(sc + L.pix_pair0);
   a.bp_cell = reinterpret_cast<const int32_t*>(sc + L.bp_cell);
   a.bp_dn = reinterpret_cast<const uint32_t*>(sc + L.bp_dn);
@@ -529,24 +474,7 @@ hipError_t launch_backward_scheduled(const Dims& d, int in_dtype, int out_dtype,
   a.per_view = d.per_view;
   a.rows = d.rows;
   a.cells = d.cells;
-  const bool al = aligned16(grad_out) && aligned16(feat) && aligned16(grad_feat);
-  if (f32) {
-    // 8 channels per lane where C allows: smaller lane groups, so more pixels
-    // (and their independent load chains) per wave
-    if (al && d.C % 8 == 0)
-      return run_pixels_nv<float, float, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-    if (al && d.C % 4 == 0)
-      return run_pixels_nv<float, float, 4>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-    return run_pixels_nv<float, float, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-  }
-  if (out_dtype == BEVPOOL_F16) {
-    if (al && d.C % 8 == 0)
-      return run_pixels_nv<half_t, half_t, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-    return run_pixels_nv<half_t, half_t, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-  }
-  if (al && d.C % 8 == 0)
-    return run_pixels_nv<half_t, float, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
-  return run_pixels_nv<half_t, float, 1>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
+  return dispatch_pixels(d, in_dtype, out_dtype, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
 }
 
 }  // namespace bevpool
