@@ -12,6 +12,7 @@ raises.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import re
 from dataclasses import dataclass
@@ -134,24 +135,31 @@ def declared_symbols(header: str = HEADER_PATH) -> list[str]:
 
 # ----------------------------------------------------------------- marshalling
 
+_DIMS = ("B", "N", "D", "H", "W", "C", "X", "Y", "Z")
+_dims = operator.itemgetter(*_DIMS)  # the sizes of a shape dict, in struct order
+
+
 def make_shape(shape) -> bevpool_shape:
     if isinstance(shape, bevpool_shape):
         return shape
+    if type(shape) is dict:
+        return bevpool_shape(*map(int, _dims(shape)))
     get = (lambda k: shape[k]) if isinstance(shape, dict) else (lambda k: getattr(shape, k))
-    return bevpool_shape(*(int(get(k)) for k in ("B", "N", "D", "H", "W", "C", "X", "Y", "Z")))
+    return bevpool_shape(*(int(get(k)) for k in _DIMS))
 
 
 def _ptr(x) -> int | None:
-    if x is None:
-        return None
     if isinstance(x, torch.Tensor):
         return x.data_ptr()
-    return int(x)
+    return None if x is None else int(x)
 
 
 def _stream(stream) -> int | None:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        if not torch.cuda.is_available():
+            return None
+        # (the raw handle: a torch.cuda.Stream object costs five times as much)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -396,7 +404,7 @@ def forward(depth: torch.Tensor, feat: torch.Tensor, plan: Plan, out_dtype=None,
             out: torch.Tensor | None = None, workspace: torch.Tensor | None = None,
             stream=None) -> torch.Tensor:
     sd = plan.shape
-    B, N, D, H, W, C, X, Y, Z = (sd[k] for k in ("B", "N", "D", "H", "W", "C", "X", "Y", "Z"))
+    B, N, D, H, W, C, X, Y, Z = _dims(sd)
     _require(depth, "depth")
     _require(feat, "feat", depth.dtype)
     if depth.dtype not in _DTYPE_CODE:
@@ -461,7 +469,7 @@ def forward_scheduled(depth: torch.Tensor, feat: torch.Tensor, sched: Schedule, 
                       stream=None) -> torch.Tensor:
     plan = sched.plan
     sd = plan.shape
-    B, N, D, H, W, C, X, Y, Z = (sd[k] for k in ("B", "N", "D", "H", "W", "C", "X", "Y", "Z"))
+    B, N, D, H, W, C, X, Y, Z = _dims(sd)
     _require(depth, "depth")
     _require(feat, "feat", depth.dtype)
     if tuple(depth.shape) != (B, N, D, H, W) or tuple(feat.shape) != (B, N, H, W, C):
@@ -499,7 +507,7 @@ def forward_scheduled_softmax(logits: torch.Tensor, feat: torch.Tensor, sched: S
     bins, formed on the fly (lse from depth_lse when not given)."""
     plan = sched.plan
     sd = plan.shape
-    B, N, D, H, W, C, X, Y, Z = (sd[k] for k in ("B", "N", "D", "H", "W", "C", "X", "Y", "Z"))
+    B, N, D, H, W, C, X, Y, Z = _dims(sd)
     _require(logits, "logits")
     _require(feat, "feat", logits.dtype)
     if tuple(logits.shape) != (B, N, D, H, W) or tuple(feat.shape) != (B, N, H, W, C):
@@ -526,7 +534,7 @@ def _check_grad_inputs(grad_out: torch.Tensor, depth: torch.Tensor, feat: torch.
     """grad_out must have out's shape (B, Z, Y, X, C) and a dtype the library
     accepts with depth's (float32 with float32; float16 or float32 with
     float16); depth and feat the plan's shapes."""
-    B, N, D, H, W, C, X, Y, Z = (sd[k] for k in ("B", "N", "D", "H", "W", "C", "X", "Y", "Z"))
+    B, N, D, H, W, C, X, Y, Z = _dims(sd)
     _require(grad_out, "grad_out")
     _require(depth, "depth")
     _require(feat, "feat", depth.dtype)
