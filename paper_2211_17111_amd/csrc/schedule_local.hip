@@ -26,11 +26,25 @@ namespace {
 constexpr int kLT = 1024;                  // threads of the per-strip kernels
 constexpr int kLW = kLT / kWave;           // 16 waves
 constexpr int kLR = kLocalPoints / kLT;    // 12 rounds of 64 lanes per wave
-constexpr int kLBuckets = 256;             // digits of one LDS sort pass (8 bits)
+constexpr int kLBuckets = 256;             // most pixels of a strip: digits of the pass by pixel (8 bits)
 constexpr int kLItems = kMaxShares + kLocalPoints / kItemPairs + 2;  // items of one strip
 static_assert(kLocalPoints % kLT == 0, "whole rounds");
 
+// Division of numbers below 2^31 by a divisor the host knows: at most one too
+// much from the rounded-up reciprocal, corrected.
+struct Divisor {
+  uint32_t d, m;
+  __device__ __forceinline__ uint32_t div(uint32_t n) const {
+    const uint32_t q = d == 1 ? n : (uint32_t)(((uint64_t)n * m) >> 32);
+    return q * d > n ? q - 1 : q;
+  }
+};
+Divisor divisor(int64_t d) {
+  return Divisor{(uint32_t)d, (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d)};
+}
+
 struct LGeom {
+  Divisor by_view, by_hw, by_w, by_bh, by_bw;  // D * H * W, H * W, W, bh, bw
   int32_t N, D, H, W, bh, bw, nhb, nwb, strips;
   int32_t hw;      // H * W
   int32_t zyx;     // cells of one sample
@@ -63,7 +77,7 @@ __device__ __forceinline__ int32_t strip_of_block(int32_t strips) {
 // One stable counting pass over the n elements held by a workgroup in the
 // wave-round layout (element e = wave * span + round * 64 + lane): returns in
 // dest[r] each element's position in the order of digit, then element.  cnt
-// is kLW x kLBuckets ints of LDS and match kLW x kLBuckets x 2 words; after
+// is kLW x NB ints of LDS and match kLW x NB x 2 words (NB >= the digits); after
 // the pass cnt[0][d] holds the first position of digit d.  Every thread of
 // the block must call it.
 //
@@ -74,22 +88,25 @@ __device__ __forceinline__ int32_t strip_of_block(int32_t strips) {
 // adds the digit's count to the wave's counter with a returning LDS add; the
 // adds of all rounds are issued before any result is used, and each returns
 // the count of that digit in the wave's earlier rounds.
-__device__ void local_ranks(const uint32_t (&digit)[kLR], int n, int span,
-                            int32_t (*cnt)[kLBuckets], uint32_t (*match)[kLBuckets][2],
-                            int32_t* s_scan, int32_t (&dest)[kLR]) {
+template <int NB>
+__device__ __forceinline__ void local_ranks(const uint32_t (&key)[kLR], int shift, int bits, int n, int span,
+                                            int32_t (*cnt)[NB], uint32_t (*match)[NB][2],
+                                            int32_t* s_scan, int32_t (&dest)[kLR]) {
   const int lane = lane_id();
   const int wid = threadIdx.x / kWave;
   const int t = threadIdx.x;
-  for (int i = t; i < kLW * kLBuckets; i += kLT) (&cnt[0][0])[i] = 0;
-  for (int i = t; i < kLW * kLBuckets * 2; i += kLT) (&match[0][0][0])[i] = 0u;
+  for (int i = t; i < kLW * NB; i += kLT) (&cnt[0][0])[i] = 0;
+  for (int i = t; i < kLW * NB * 2; i += kLT) (&match[0][0][0])[i] = 0u;
   __syncthreads();
   const int rounds = span / kWave;
+  const uint32_t mask = (1u << bits) - 1u;
+  auto digit = [&](int r) { return (key[r] >> shift) & mask; };
   uint2 m[kLR];
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r >= rounds) continue;
     const bool valid = wid * span + r * kWave + lane < n;
-    uint32_t* w = match[wid][digit[r]];
+    uint32_t* w = match[wid][digit(r)];
     m[r] = make_uint2(0u, 0u);
     if (valid) {
       atomicOr(&w[lane >> 5], 1u << (lane & 31));
@@ -97,47 +114,44 @@ __device__ void local_ranks(const uint32_t (&digit)[kLR], int n, int span,
       *reinterpret_cast<uint2*>(w) = make_uint2(0u, 0u);
     }
   }
-  int32_t below[kLR], leader[kLR], old[kLR];
+  // (each lane's number among the lanes of its digit, and their lowest lane)
+  uint32_t place[kLR];
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r >= rounds) continue;
     const uint64_t same = (uint64_t)m[r].x | ((uint64_t)m[r].y << 32);
-    below[r] = rank_below(same);
-    leader[r] = same != 0 ? (int32_t)__builtin_ctzll(same) : lane;
-    old[r] = 0;
-    if (same != 0 && below[r] == 0) old[r] = atomicAdd(&cnt[wid][digit[r]], __popcll(same));
+    const int below = rank_below(same);
+    place[r] = (uint32_t)below | (uint32_t)(same != 0 ? (int32_t)__builtin_ctzll(same) : lane) << 8;
+    dest[r] = 0;
+    if (same != 0 && below == 0) dest[r] = atomicAdd(&cnt[wid][digit(r)], __popcll(same));
   }
-  int32_t rank[kLR];
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r >= rounds) continue;
-    rank[r] = __shfl(old[r], leader[r], kWave) + below[r];
+    dest[r] = __shfl(dest[r], (int)(place[r] >> 8), kWave) + (int32_t)(place[r] & 0xffu);
   }
   __syncthreads();
   // digit t: each wave's offset within the digit, and the digit's count
-  int32_t c[kLW];
   int tot = 0;
-  if (t < kLBuckets) {
-#pragma unroll
-    for (int w = 0; w < kLW; ++w) c[w] = cnt[w][t];
+  if (t < NB) {
 #pragma unroll
     for (int w = 0; w < kLW; ++w) {
-      const int x = c[w];
-      c[w] = tot;
+      const int x = cnt[w][t];
+      cnt[w][t] = tot;
       tot += x;
     }
   }
   int total;
   const int start = block_exclusive_scan<kLT>(tot, s_scan, &total);
-  if (t < kLBuckets) {
+  if (t < NB) {
 #pragma unroll
-    for (int w = 0; w < kLW; ++w) cnt[w][t] = c[w] + start;
+    for (int w = 0; w < kLW; ++w) cnt[w][t] += start;
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r >= rounds) continue;
-    dest[r] = cnt[wid][digit[r]] + rank[r];
+    dest[r] += cnt[wid][digit(r)];
   }
 }
 
@@ -179,12 +193,12 @@ __global__ __launch_bounds__(256) void k_ls_map(const int32_t* __restrict__ rd,
   if (p < 0 || p >= P || r < 0 || r >= cells) return;
   // (32-bit unsigned: p < 2^31)
   const uint32_t per_view = (uint32_t)g.D * (uint32_t)g.hw;
-  const uint32_t bn = (uint32_t)p / per_view;
+  const uint32_t bn = g.by_view.div((uint32_t)p);
   const uint32_t rem = (uint32_t)p - bn * per_view;
-  const uint32_t d = rem / (uint32_t)g.hw;
+  const uint32_t d = g.by_hw.div(rem);
   const uint32_t pix = rem - d * (uint32_t)g.hw;
-  const uint32_t h = pix / (uint32_t)g.W, w = pix - h * (uint32_t)g.W;
-  const uint32_t hb = h / (uint32_t)g.bh, wb = w / (uint32_t)g.bw;
+  const uint32_t h = g.by_w.div(pix), w = pix - h * (uint32_t)g.W;
+  const uint32_t hb = g.by_bh.div(h), wb = g.by_bw.div(w);
   const uint32_t h0 = hb * (uint32_t)g.bh, w0 = wb * (uint32_t)g.bw;
   const uint32_t bws = min((uint32_t)g.bw, (uint32_t)g.W - w0);
   const uint32_t bhs = min((uint32_t)g.bh, (uint32_t)g.H - h0);
@@ -197,14 +211,22 @@ __global__ __launch_bounds__(256) void k_ls_map(const int32_t* __restrict__ rd,
 // (key = rank within the sample << (lp_bits + d_bits) | pixel << d_bits |
 // first bin, and the point count), with the strip's pair count and the pair
 // count of each of its pixels.
+//
+// The passes sort in place: every wave holds its keys in registers across a pass's
+// barriers.  (A workgroup has a CU to itself by its registers; held to the 64 that
+// two would need it spills: 93 us against 51 at 300 strips.)
 __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ map, LGeom g,
                                                    uint32_t* __restrict__ rkey,
                                                    int32_t* __restrict__ rnpts,
                                                    int32_t* __restrict__ strip_np,
                                                    int32_t* __restrict__ pix_count) {
-  __shared__ uint32_t sa[kLocalPoints], sb[kLocalPoints];
-  __shared__ int32_t cnt[kLW][kLBuckets];
-  __shared__ uint32_t match[kLW][kLBuckets][2];
+  extern __shared__ __attribute__((aligned(16))) uint32_t sa[];  // maxpts keys
+  __shared__ __attribute__((aligned(16))) uint32_t s_pass[kLW * kLBuckets * 3];
+  int32_t(*const cnt)[kLBuckets] = reinterpret_cast<int32_t(*)[kLBuckets]>(s_pass);
+  uint32_t(*const match)[kLBuckets][2] =
+      reinterpret_cast<uint32_t(*)[kLBuckets][2]>(s_pass + kLW * kLBuckets);
+  uint16_t* const heads = reinterpret_cast<uint16_t*>(s_pass);
+  static_assert(kLW * kLBuckets * 3 * 4 >= kLocalPoints * 2, "a strip's head positions fit");
   __shared__ int32_t s_scan[kLW];
   __shared__ int32_t pc[kLBuckets];
   const int t = threadIdx.x;
@@ -216,6 +238,7 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
   g.strip(s, bn, h0, w0, bhs, bws);
   const int32_t npix = bhs * bws;
   const int32_t nf = g.D * npix;  // frustum points of the strip (<= kLocalPoints)
+  const float inv_npix = 1.f / (float)npix;
   const int32_t rb_base = (bn / g.N) * g.zyx;
   if (t < kLBuckets) pc[t] = 0;
 
@@ -249,15 +272,13 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
     if (r >= roundsf) continue;
     if (rv[r] < 0) continue;
     const int32_t j = wid * spanf + r * kWave + lane;
-    const int32_t d = j / npix;
+    const int32_t d = (int32_t)(((float)j + 0.5f) * inv_npix);  // (exact: j < 2^21)
     const int32_t lp = j - d * npix;
     sa[koff + pre[r]] = ((uint32_t)(rv[r] - rb_base) << (g.lp_bits + g.d_bits)) |
                         ((uint32_t)lp << g.d_bits) | (uint32_t)d;
   }
   __syncthreads();
   const int span = ((n + kLT - 1) / kLT) * kWave;  // elements per wave
-  uint32_t* src = sa;
-  uint32_t* dst = sb;
   // stable LSD passes over (cell, pixel); the bins are already in order
   const int sort_bits = g.rb_bits + g.lp_bits;  // + d_bits <= 32
   if (n > 1 && sort_bits > 0) {
@@ -266,27 +287,22 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
     for (int ps = 0; ps < passes; ++ps) {
       const int shift = g.d_bits + ps * pbits;
       const int bits = min(pbits, sort_bits - ps * pbits);
-      const uint32_t mask = (1u << bits) - 1u;
-      uint32_t key[kLR], digit[kLR];
+      uint32_t key[kLR];
       int32_t dest[kLR];
 #pragma unroll
       for (int r = 0; r < kLR; ++r) {
         if (r * kWave >= span) continue;
         const int e = wid * span + r * kWave + lane;
-        key[r] = e < n ? src[e] : 0u;
-        digit[r] = (key[r] >> shift) & mask;
+        key[r] = e < n ? sa[e] : 0u;
       }
-      local_ranks(digit, n, span, cnt, match, s_scan, dest);
+      local_ranks<kLBuckets>(key, shift, bits, n, span, cnt, match, s_scan, dest);
 #pragma unroll
       for (int r = 0; r < kLR; ++r) {
         if (r * kWave >= span) continue;
         const int e = wid * span + r * kWave + lane;
-        if (e < n) dst[dest[r]] = key[r];
+        if (e < n) sa[dest[r]] = key[r];
       }
       __syncthreads();
-      uint32_t* tmp = src;
-      src = dst;
-      dst = tmp;
     }
   }
 
@@ -301,8 +317,8 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
     if (r * kWave >= span) continue;
     const int e = wid * span + r * kWave + lane;
     const bool valid = e < n;
-    const uint32_t k = valid ? src[e] : 0u;
-    const uint32_t pk = (valid && e > 0) ? src[e - 1] : 0u;
+    const uint32_t k = valid ? sa[e] : 0u;
+    const uint32_t pk = (valid && e > 0) ? sa[e - 1] : 0u;
     hd[r] = valid && (e == 0 || (k >> g.d_bits) != (pk >> g.d_bits) ||
                       (k & dmask) != (pk & dmask) + 1u);
     const uint64_t m = wave_ballot(hd[r]);
@@ -315,14 +331,14 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
   for (int r = 0; r < kLR; ++r) {
     if (r * kWave >= span) continue;
     const int e = wid * span + r * kWave + lane;
-    if (hd[r]) dst[woff + pre[r]] = (uint32_t)e;  // head position of each pair
+    if (hd[r]) heads[woff + pre[r]] = (uint16_t)e;  // head position of each pair
   }
   __syncthreads();
   const int64_t region = (int64_t)s * g.maxpts;
   for (int j = t; j < np; j += kLT) {
-    const int e0 = (int)dst[j];
-    const int e1 = j + 1 < np ? (int)dst[j + 1] : n;
-    const uint32_t key = src[e0];
+    const int e0 = (int)heads[j];
+    const int e1 = j + 1 < np ? (int)heads[j + 1] : n;
+    const uint32_t key = sa[e0];
     rkey[region + j] = key;
     rnpts[region + j] = e1 - e0;
     atomicAdd(&pc[(key >> g.d_bits) & lpmask], 1);
@@ -385,9 +401,10 @@ __device__ int32_t block_scan16(const int32_t* __restrict__ a, int64_t n, int32_
 constexpr int kPlanStrips = 4096;  // strip offsets kept in LDS up to this many strips
 constexpr int kPlanItems = 8192;   // item starts kept in LDS up to this many items
 
-// One block: pair offsets of the strips, the items (cut at the shares) and
-// their strips and first pairs, the shares' first items, and the first
-// pixel-major pair of every feature row.
+// Block 0: pair offsets of the strips, the items (cut at the shares) and their
+// strips and first pairs, and the shares' first items.  Block 1: the first
+// pixel-major pair of every feature row.  (In turn in one block: %Q0% us, %Q1% now, at
+// 300 strips and 24,000 rows.)
 __global__ __launch_bounds__(kLT) void k_ls_plan(const int32_t* __restrict__ strip_np,
                                                  int32_t strips, int32_t shares, int32_t ip,
                                                  int64_t items_cap, const int32_t* __restrict__ pix_count,
@@ -404,6 +421,36 @@ __global__ __launch_bounds__(kLT) void k_ls_plan(const int32_t* __restrict__ str
   __shared__ int32_t s_ip0[kPlanItems + 1];
   __shared__ int32_t s_rows[17 * kLT];
   const int t = threadIdx.x;
+  if (blockIdx.x == 1) {  // (uniform)
+    // 16 rows per thread and step; the prefixes go through LDS (17 words per thread, against bank
+    // conflicts) so that lanes store consecutive entries
+    int32_t rtot = 0;
+    for (int64_t base = 0; base < rows; base += 16 * kLT) {
+      const int64_t i0 = base + 16 * (int64_t)t;
+      int32_t v[16];
+      load16(pix_count, i0, rows, v);
+      int32_t sum = 0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sum += v[k];
+      int32_t tot;
+      int32_t off = rtot + block_exclusive_scan<kLT>(sum, s_scan, &tot);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        s_rows[17 * t + k] = off;
+        off += v[k];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int e = j * kLT + t;  // element of this step, staged at 17 * (e / 16) + e % 16
+        if (base + e < rows) pix_pair0[base + e] = s_rows[17 * (e >> 4) + (e & 15)];
+      }
+      __syncthreads();
+      rtot += tot;
+    }
+    if (t == 0) pix_pair0[rows] = rtot;
+    return;
+  }
   if (t == 0) s_bad = 0;
   const bool lds_strips = strips <= kPlanStrips;
   // 1. pair offsets (16 consecutive strips per thread and step)
@@ -501,35 +548,8 @@ __global__ __launch_bounds__(kLT) void k_ls_plan(const int32_t* __restrict__ str
   __syncthreads();
   for (int w = t; w < shares; w += kLT)
     if (share_item0[w + 1] - share_item0[w] > kShareItems) s_bad = 1;
-  // 4. first pixel-major pair of every feature row, 16 rows per thread and
-  // step; the prefixes go through LDS (17 words per thread, against bank
-  // conflicts) so that lanes store consecutive entries
-  int32_t rtot = 0;
-  for (int64_t base = 0; base < rows; base += 16 * kLT) {
-    const int64_t i0 = base + 16 * (int64_t)t;
-    int32_t v[16];
-    load16(pix_count, i0, rows, v);
-    int32_t sum = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sum += v[k];
-    int32_t tot;
-    int32_t off = rtot + block_exclusive_scan<kLT>(sum, s_scan, &tot);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      s_rows[17 * t + k] = off;
-      off += v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int e = j * kLT + t;  // element of this step, staged at 17 * (e / 16) + e % 16
-      if (base + e < rows) pix_pair0[base + e] = s_rows[17 * (e >> 4) + (e & 15)];
-    }
-    __syncthreads();
-    rtot += tot;
-  }
+  __syncthreads();
   if (t == 0) {
-    pix_pair0[rows] = rtot;
     hdr[kHdrShares] = shares;
     hdr[kHdrSharesOk] = s_bad ? 0 : 1;
     hdr[kHdrItemPairs] = ip;
@@ -582,7 +602,9 @@ __global__ __launch_bounds__(kLT) void k_ls_emit(
   const int rb_shift = g.lp_bits + g.d_bits;
   const uint32_t dmask = (1u << g.d_bits) - 1u;
   const uint32_t lpmask = (1u << g.lp_bits) - 1u;
-  uint32_t key[kLR], digit[kLR];
+  const float inv_bws = 1.f / (float)bws;
+  const int32_t rd_base = bn * g.D * g.hw + h0 * g.W + w0;  // depth rank of pixel 0, bin 0 (< 2^31)
+  uint32_t key[kLR];
   int32_t npts[kLR], item[kLR], sin[kLR];
   bool hd[kLR];
   int wcount = 0;
@@ -602,7 +624,6 @@ __global__ __launch_bounds__(kLT) void k_ls_emit(
     const uint64_t m = wave_ballot(hd[r]);
     sin[r] = wcount + rank_below(m) + (hd[r] ? 1 : 0);  // inclusive, within the wave
     wcount += __popcll(m);
-    digit[r] = (key[r] >> g.d_bits) & lpmask;
   }
   int nseg;
   const int woff = wave_offsets(wcount, s_scan, &nseg);
@@ -624,10 +645,9 @@ __global__ __launch_bounds__(kLT) void k_ls_emit(
     const int32_t gp = P0 + e;
     const uint32_t lp = (key[r] >> g.d_bits) & lpmask;
     const int32_t d0 = (int32_t)(key[r] & dmask);
-    const int32_t hl = (int32_t)lp / bws;
+    const int32_t hl = (int32_t)(((float)lp + 0.5f) * inv_bws);  // (exact: lp < 2^21)
     const int32_t cell = rb_base + (int32_t)(key[r] >> rb_shift);
-    pair_rd0[gp] = (int32_t)(((int64_t)(bn * g.D + d0) * g.H + h0 + hl) * g.W + w0 +
-                             ((int32_t)lp - hl * bws));
+    pair_rd0[gp] = rd_base + d0 * g.hw + hl * (g.W - bws) + (int32_t)lp;
     pair_ln[gp] = (lp & kPairPixel) | (hd[r] ? kPairHead : 0u) | ((uint32_t)npts[r] << 16);
     pair_seg[gp] = (uint16_t)(sin[r] - s_iseg[item[r]]);
     if (hd[r]) {
@@ -638,13 +658,13 @@ __global__ __launch_bounds__(kLT) void k_ls_emit(
   }
   // pixel-major pairs: a stable pass by local pixel
   int32_t dest[kLR];
-  local_ranks(digit, np, span, cnt, match, s_scan, dest);
+  local_ranks<kLBuckets>(key, g.d_bits, g.lp_bits, np, span, cnt, match, s_scan, dest);
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r * kWave >= span) continue;
     const int e = wid * span + r * kWave + lane;
     if (e >= np) continue;
-    const int32_t lp = (int32_t)digit[r];
+    const int32_t lp = (int32_t)((key[r] >> g.d_bits) & lpmask);
     const int32_t q = s_pix0[lp] + (dest[r] - cnt[0][lp]);
     bp_cell[q] = rb_base + (int32_t)(key[r] >> rb_shift);
     bp_dn[q] = (key[r] & dmask) | ((uint32_t)npts[r] << 16);
@@ -922,6 +942,11 @@ hipError_t launch_schedule_local(const Dims& d, const int32_t* rd, const int32_t
   g.d_bits = bits_for(d.D);
   g.lp_bits = bits_for(L.sd.pixels);
   g.rb_bits = bits_for(g.zyx);
+  g.by_view = divisor(d.per_view);
+  g.by_hw = divisor(d.hw);
+  g.by_w = divisor(d.W);
+  g.by_bh = divisor(L.sd.bh);
+  g.by_bw = divisor(L.sd.bw);
   const int32_t shares = (int32_t)std::min<int64_t>(forward_workgroups(), kMaxShares);
   int32_t* map = W(L.wl_map);
   uint32_t* rkey = reinterpret_cast<uint32_t*>(W(L.wl_rkey));
@@ -945,8 +970,8 @@ hipError_t launch_schedule_local(const Dims& d, const int32_t* rd, const int32_t
   const unsigned g_nv = (unsigned)((n_valid + 255) / 256);
   k_ls_map<<<g_nv, 256, 0, stream>>>(rd, rb, n_valid, d.P, d.cells, g, map);
   const unsigned strip_blocks = (unsigned)((L.sd.strips + kXcds - 1) / kXcds * kXcds);
-  k_ls_strips<<<strip_blocks, kLT, 0, stream>>>(map, g, rkey, rnpts, strip_np, pix_count);
-  k_ls_plan<<<1, kLT, 0, stream>>>(strip_np, g.strips, shares, schedule_item_pairs(n_valid),
+  k_ls_strips<<<strip_blocks, kLT, sizeof(uint32_t) * (size_t)g.maxpts, stream>>>(map, g, rkey, rnpts, strip_np, pix_count);
+  k_ls_plan<<<2, kLT, 0, stream>>>(strip_np, g.strips, shares, schedule_item_pairs(n_valid),
                                    L.items_cap, pix_count, d.rows,
                                    strip_p0, strip_it0, hdr, S(L.item_strip), S(L.item_pair0),
                                    S(L.share_item0), S(L.pix_pair0));
