@@ -9,6 +9,15 @@
 
 namespace bevpool {
 
+// floor(n / d) for 0 <= n < 2^42 and 0 < d < 2^31, quotient below 2^31.  The
+// float64 quotient is off by at most n / d 2^-53 <= 2^-11 / d and the next integer
+// above an inexact one is at least 1 / d away.  (The 64-bit integer division of
+// the compiler is a hundred instructions, and the few threads that cut strips
+// into items run a chain of them.)
+__device__ __forceinline__ int32_t div_floor(int64_t n, int64_t d) {
+  return (int32_t)((double)n / (double)d);
+}
+
 // Share boundary w, floor(P * w / S), moved to the start or end of the strip
 // [a, b) it falls in when within kMinPiece pairs of it, so that no item is
 // a small remnant of a strip.
@@ -26,16 +35,16 @@ template <typename F>
 __device__ int64_t strip_items(int64_t a, int64_t b, int64_t P, int64_t S, int64_t ip, F visit) {
   // shares w with a < floor(P w / S) < b: floor(P w / S) > a  <=>
   // w >= ceil((a + 1) S / P); floor(P w / S) < b  <=>  w < ceil(b S / P)
-  const int64_t w_lo = ((a + 1) * S + P - 1) / P;
-  const int64_t w_hi = (b * S + P - 1) / P - 1;
+  const int64_t w_lo = div_floor((a + 1) * S + P - 1, P);
+  const int64_t w_hi = div_floor(b * S + P - 1, P) - 1;
   int64_t n = 0;
   int64_t q = a;
   for (int64_t w = w_lo; w <= w_hi + 1; ++w) {
-    const int64_t e = w <= w_hi ? snap_bound((P * w) / S, a, b) : b;  // end of this piece
+    const int64_t e = w <= w_hi ? snap_bound(div_floor(P * w, S), a, b) : b;  // end of this piece
     const int64_t L = e - q;
     if (L > 0) {
-      const int64_t K = (L + ip - 1) / ip;
-      for (int64_t i = 0; i < K; ++i) visit(n + i, q + (i * L) / K);
+      const int64_t K = div_floor(L + ip - 1, ip);
+      for (int64_t i = 0; i < K; ++i) visit(n + i, q + div_floor(i * L, K));
       n += K;
       q = e;
     }
