@@ -53,9 +53,10 @@ METRIC = "BEV-pool fwd latency (ms) + achieved HBM GB/s at 6×640×1600, D=118, 
 HBM_PEAK_GBS = 8000.0
 MALL_BYTES = 256 * 2 ** 20
 PMC_FILE = os.path.join(ROOT, "profiles", "forward_headline_traffic.txt")
-# kernels of each forward path (the interval path is two launches, timed together)
-FORWARD_KERNELS = {"interval": "k_fwd_ranges+k_fwd_cells", "strips": "k_fwd_strips+k_fwd_combine"}
-FORWARD_SOURCES = ("forward.hip", "forward_strips.hip", "internal.h", "vec.h", "device_utils.h")
+# kernels of each forward path at the default workload (two launches, timed together)
+FORWARD_KERNELS = {"interval": "k_fwd_ranges+k_fwd_cells", "strips": "k_fwd_dense+k_fwd_combine"}
+FORWARD_SOURCES = ("forward.hip", "forward_strips.hip", "forward_dense.hip", "strip_args.h", "internal.h", "vec.h",
+                   "device_utils.h")
 
 
 def log(msg):
