@@ -49,7 +49,7 @@ constexpr int kSegTile = 16;         // segments of one matrix tile
 constexpr int kChunkC = 256;         // channels staged at a time
 constexpr int kMaxSegs = 192;        // most segments of the index table
 constexpr int kMaxRank = 254;        // most pairs of a segment the index table numbers
-constexpr int kMinPoints = 18;           // points per segment from which the products pay
+constexpr int kMinPoints = 18;       // points per segment from which the products pay
 // LDS of a workgroup (less the kernel's own and the allocation's granule):
 // three to a CU; two where the items are too few to need the third
 constexpr int kDenseLds = 160 * 1024 / 3 - 2304;
@@ -539,11 +539,13 @@ hipError_t run_tiles(const Dims& d, const DenseArgs& s, int mt, size_t lds, cons
 // in float32 but 45.4 / 47.3 us in float16; 10 (256x704) 14.2 / 17.4 us; 2.7
 // (voxels) 74.4 / 74.3 us.
 // The index numbers a segment's pairs in a byte, so strips have at most
-// kMaxRank pixels (narrower strips than those of 32 channels and fewer).
+// kMaxRank pixels (narrower strips than those of 32 channels and fewer).  A
+// view's depth scores and a strip's rows are reached by 32-bit byte offsets.
 bool dense_forward_ok(const Dims& d, const StripDims& sd, bool half_in, int32_t n_valid, int32_t n_intervals,
                       int32_t n_slots) {
-  const int64_t view_bytes = d.D * d.hw * (half_in ? 2 : 4);
-  return sd.pixels <= kMaxRank && view_bytes < ((int64_t)1 << 31) &&
+  const int64_t elem = half_in ? 2 : 4;
+  const int64_t view_bytes = d.D * d.hw * elem, strip_bytes = (sd.bh + 1) * d.W * d.C * elem;
+  return sd.pixels <= kMaxRank && view_bytes < ((int64_t)1 << 31) && strip_bytes < ((int64_t)1 << 31) &&
          n_valid >= (int64_t)kMinPoints * ((int64_t)n_intervals + n_slots);
 }
 

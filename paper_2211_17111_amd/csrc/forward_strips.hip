@@ -9,7 +9,9 @@
 // image instead of the grid: every feature row is read from memory once per
 // item, every pair (one cell, one pixel, a run of consecutive depth bins)
 // reads its row from LDS, and only the cells a strip shares with its
-// neighbours need a second pass.
+// neighbours need a second pass.  Schedules whose segments hold many points
+// are pooled by k_fwd_dense (dense_forward_ok), the others by k_fwd_strips;
+// k_fwd_combine follows either.
 //
 //   k_fwd_strips   one persistent workgroup per compute unit and channel
 //                  chunk (up to 64 vectors), taking one share of the items
@@ -71,6 +73,7 @@ constexpr int kPairBatch = 8;   // pair records per loading thread in flight
 constexpr int buf_bytes(int ip) { return kStripBytes + ip * 12; }
 constexpr int kHdrCache = 128;  // item headers of a workgroup kept in LDS
 constexpr int kCombThreads = 256;
+constexpr int kCombBatch = 8;   // slots of a cell in flight where it has that many
 static_assert(kStripBytes % (16 * kLoadThreads) == 0, "row vectors split evenly over the loading threads");
 static_assert(kItemPairs % kNT == 0 && kItemPairs % kLoadThreads == 0 &&
                   kItemPairsBig % kNT == 0 && kItemPairsBig % kLoadThreads == 0,
@@ -742,11 +745,20 @@ __global__ __launch_bounds__(kNT) void k_fwd_strips(const TIn* __restrict__ dept
   combine_parts(b ^ 1, kNT);  // the last item's, by every wave
 }
 
+// Cells that k_fwd_combine may have to add up: a cell in slots has two or more.
+__host__ __device__ __forceinline__ int32_t comb_cap(const StripArgs& a) { return a.n_occ < a.n_slots / 2 ? a.n_occ : a.n_slots / 2; }
+
+// One lane group per cell that may be in slots and per empty cell.  It is bound
+// by its two dependent round trips (records beside the header, then slots) and,
+// with many cells, by the slots' bytes.  Without the header's round trip before
+// the records, without the groups of the cells stored directly and with eight
+// slots of a cell in flight instead of four: 640x1600 6.8 -> 5.6 us, eight
+// samples at 256x704 10.2 -> 7.5, four float16 frames 13.0 -> 11.0, voxels 27.2 ->
+// 25.6 (sixteen in flight: 5.5, 7.6, 11.0 and 26.1).
 template <typename TOut, int VEC>
 __global__ __launch_bounds__(kCombThreads) void k_fwd_combine(TOut* __restrict__ out,
                                                               StripArgs a) {
   const int32_t* hdr = a.hdr;
-  const bool ok = header_ok(a);
   const int lane = lane_id();
   const int C = a.C;
   const int CV = C / VEC;
@@ -757,33 +769,37 @@ __global__ __launch_bounds__(kCombThreads) void k_fwd_combine(TOut* __restrict__
   const int vi = lane - lg * cvc;
   if (lg >= gpw) return;
   const int64_t j = ((int64_t)blockIdx.x * (kCombThreads / kWave) + threadIdx.x / kWave) * gpw + lg;
+  const int64_t col = (int64_t)(cbase + vi) * VEC;
+  // Groups below `cap` add up a cell, the n_empty after them clear one: roles
+  // that the launch's own counts give, so that the records come with the
+  // header and not after it.
+  const int64_t cap = comb_cap(a);
+  const bool comb = j < cap;
+  int32_t cell = -1, s0 = 0, s1 = 0;
+  if (comb) {
+    cell = a.comb_cell[j];
+    s0 = a.comb_slot0[j];
+    s1 = a.comb_slot0[j + 1];
+  } else if (j - cap < a.n_empty) {
+    cell = a.empty[j - cap];
+  }
+  const int32_t n_comb = hdr[kHdrComb], n_empty = hdr[kHdrEmpty];
+  const bool ok = header_ok(a) && n_comb <= cap;
+  // (an empty asm reading the records: the compiler would otherwise move their
+  // loads behind the header's test)
+  asm volatile("" ::"v"(cell), "v"(s0), "v"(s1));
   if (!ok) {
     // a schedule that does not hold the launch's counts: every cell is NaN
-    // (the grid has a lane group per cell and channel chunk)
-    if (j < a.cells) {
-      float nan[VEC];
+    const int64_t groups = (int64_t)gridDim.x * (kCombThreads / kWave) * gpw;
+    float nan[VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) nan[e] = __builtin_nanf("");
-      Vec<TOut, VEC>::store(out + j * C + (int64_t)(cbase + vi) * VEC, nan);
-    }
+    for (int e = 0; e < VEC; ++e) nan[e] = __builtin_nanf("");
+    for (int64_t c = j; c < a.cells; c += groups) Vec<TOut, VEC>::store(out + c * C + col, nan);
     return;
   }
-  const int64_t n_comb = min(hdr[kHdrComb], a.n_occ);
-  const int64_t n_empty = min<int64_t>(hdr[kHdrEmpty], a.n_empty);
-  const int64_t col = (int64_t)(cbase + vi) * VEC;
-  if (j >= n_comb + n_empty) return;
-  // Both roles' records are read at once, unconditionally (clamped index),
-  // so that a cell and its slot range arrive together: a load behind a test
-  // of the cell would cost another round trip.
-  const int64_t jc = min(j, n_comb > 0 ? n_comb - 1 : 0);
-  const int64_t cell_c = a.comb_cell[jc];
-  const int64_t s0 = a.comb_slot0[jc], s1 = a.comb_slot0[jc + 1];
-  const int64_t cell_e = a.empty[min(max(j - n_comb, (int64_t)0), n_empty > 0 ? n_empty - 1 : 0)];
-  // (an empty asm reading all four values: the compiler would otherwise move
-  // each load into the branch that uses it, behind the previous one's test)
-  asm volatile("" ::"v"((int32_t)cell_c), "v"((int32_t)s0), "v"((int32_t)s1), "v"((int32_t)cell_e));
-  if (j < n_comb) {
-    if (cell_c < 0 || cell_c >= a.cells) return;
+  if (cell < 0 || cell >= a.cells) return;
+  if (comb) {
+    if (j >= n_comb) return;
     float sum[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) sum[e] = 0.f;
@@ -792,34 +808,41 @@ __global__ __launch_bounds__(kCombThreads) void k_fwd_combine(TOut* __restrict__
 #pragma unroll
       for (int e = 0; e < VEC; ++e) sum[e] = __builtin_nanf("");
     } else {
-      int64_t s = s0;
-      for (; s + 4 <= s1; s += 4) {
-        float t[4][VEC];
+      const float* p = a.slots + (int64_t)s0 * C + col;
+      int left = s1 - s0;
+      auto add = [&](auto n_tag) {
+        constexpr int N = decltype(n_tag)::value;
+        float t[N][VEC];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) Vec<float, VEC>::load(a.slots + (s + k) * C + col, t[k]);
+        for (int k = 0; k < N; ++k) Vec<float, VEC>::load(p + (int64_t)k * C, t[k]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < N; ++k)
 #pragma unroll
           for (int e = 0; e < VEC; ++e) sum[e] += t[k][e];
-      }
+        p += (int64_t)N * C;
+        left -= N;
+      };
+#pragma unroll 1
+      while (left >= kCombBatch) add(std::integral_constant<int, kCombBatch>{});
+#pragma unroll 1
+      while (left >= 4) add(std::integral_constant<int, 4>{});
       // the last 1-3 slots (most cells have 2 or 3), loaded together
-      const int rest = (int)(s1 - s);
       float t[3][VEC];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) t[k][e] = 0.f;
-        if (k < rest) Vec<float, VEC>::load(a.slots + (s + k) * C + col, t[k]);
+        if (k < left) Vec<float, VEC>::load(p + (int64_t)k * C, t[k]);
       }
 #pragma unroll
       for (int k = 0; k < 3; ++k)
-        if (k < rest)
+        if (k < left)
 #pragma unroll
           for (int e = 0; e < VEC; ++e) sum[e] += t[k][e];
     }
-    Vec<TOut, VEC>::store(out + cell_c * C + col, sum);
-  } else if (cell_e >= 0 && cell_e < a.cells) {
-    store_zero<TOut, VEC>(out + cell_e * C + col);
+    Vec<TOut, VEC>::store(out + (int64_t)cell * C + col, sum);
+  } else if (j - cap < n_empty) {
+    store_zero<TOut, VEC>(out + (int64_t)cell * C + col);
   }
 }
 
@@ -851,13 +874,12 @@ hipError_t run(const Dims& d, const StripDims& sd, const void* depth, const void
     k_fwd_strips<TIn, TOut, VEC, SM, kItemPairs><<<dim3((unsigned)blocks, chunks), dim3(kNT), 0, stream>>>(
         static_cast<const TIn*>(depth), static_cast<const TIn*>(feat), o, a);
   const int64_t gpw = kWave / (CV < kWave ? CV : kWave);
-  const int64_t entries = (int64_t)a.n_occ + a.n_empty;
+  // (at least one block, which marks a schedule of other counts)
+  const int64_t entries = std::max<int64_t>((int64_t)comb_cap(a) + a.n_empty, 1);
   const int64_t per_block = gpw * (kCombThreads / kWave);
   const int64_t cblocks = (entries + per_block - 1) / per_block;
   const unsigned cchunks = (unsigned)((CV + kWave - 1) / kWave);
-  if (cblocks > 0)
-    k_fwd_combine<TOut, VEC><<<dim3((unsigned)cblocks, cchunks), dim3(kCombThreads), 0, stream>>>(
-        o, a);
+  k_fwd_combine<TOut, VEC><<<dim3((unsigned)cblocks, cchunks), dim3(kCombThreads), 0, stream>>>(o, a);
   return hipGetLastError();
 }
 
