@@ -407,6 +407,26 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
           else acc[m] = mfma_16x16x4(x[m], w, acc[m]);
         }
       };
+      // For a float32 result the products of two steps are summed from zero and
+      // then added: a sum has fewer roundings in a chain.  Error against float64 at
+      // 640x1600: 1.3e-7 through one accumulator, 8.5e-8 so (the walk: 1.1e-7), at
+      // 24.6 and 25.6 us a forward.  A float16 result's own rounding (2.1e-4) is far
+      // above either.  (Two accumulators: 1.0e-7, but they spill: 32.1 us.)
+      constexpr bool kTwoSteps = sizeof(TOut) == 4;
+      auto multiply_two = [&](const Raw (&xa)[kRaws], float wa, const Raw (&xb)[kRaws], float wb) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          float4_t two = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (kHalf) {
+            two = mfma_16x16x4((float)xa[m / 2][m % 2], wa, two);
+            two = mfma_16x16x4((float)xb[m / 2][m % 2], wb, two);
+          } else {
+            two = mfma_16x16x4(xa[m], wa, two);
+            two = mfma_16x16x4(xb[m], wb, two);
+          }
+          acc[m] += two;
+        }
+      };
       Raw x0[kRaws], x1[kRaws];
       // the products of one step run while the features of the next, the weights
       // of the two after it and the bytes of the two after those are read
@@ -416,24 +436,33 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
       r0 = ip[8];
       r1 = ip[12];
       read(x0);
+      if constexpr (kTwoSteps) read(x1);
 #pragma unroll 1
       for (; st < st_end; st += 2) {
-        read(x1);
+        if constexpr (!kTwoSteps) read(x1);
         const float v0 = wseg[r0], v1 = wseg[r1];
         const uint32_t q0 = r0, q1 = r1;
         r0 = ip[16];
         r1 = ip[20];
         ip += 8;
-        multiply(x0, w0);
-        read(x0);
-        multiply(x1, w1);
+        if constexpr (kTwoSteps) {
+          multiply_two(x0, w0, x1, w1);
+          read(x0);
+          read(x1);
+        } else {
+          multiply(x0, w0);
+          read(x0);
+          multiply(x1, w1);
+        }
         w0 = weight(q0, v0);
         w1 = weight(q1, v1);
+        if constexpr (!kTwoSteps) {  // (the order above needs registers that the two-step form does not have)
 #pragma unroll
-        for (int m = 0; m < 2 * MT; ++m) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
-          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // vector operations
+          for (int m = 0; m < 2 * MT; ++m) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // a product
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // vector operations
+          }
         }
       }
       // ---- this lane's sums: channels c0 .. of each tile (two float16 tiles
