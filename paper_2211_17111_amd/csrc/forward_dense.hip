@@ -27,7 +27,7 @@
 // resident at once (three workgroups of 8 waves to a CU, by LDS and at most 80
 // VGPRs); with many items (four frames) the issue of vector instructions, about
 // 50 per pair, and 13 us of matrix time.  k_fwd_strips against this kernel,
-// kernel time: 640x1600 float32 25.5 -> 19.5 us, from logits 32.8 -> 21.5 us;
+// kernel time: 640x1600 float32 25.5 -> 22.2 us, from logits 32.8 -> 22.1 us;
 // four frames at 640x1760, float16, 116 -> 67 us.
 
 #include "device_utils.h"
