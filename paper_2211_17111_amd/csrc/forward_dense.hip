@@ -469,17 +469,17 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
       // interleave), 4 or 8 at a time
       const int64_t base = (dest >= 0 ? (int64_t)dest : (int64_t)~dest) * C + cbase;
       const bool mine = seg < nseg && (dest >= 0 ? dest < a.cells : (int64_t)~dest < a.slot_cap);
+      // (channels from cc on are sums of what LDS holds past the rows: neither
+      // stored nor looked at)
+      float bad = 0.f;
       auto put = [&](int c, auto n_tag, const float* sum) {
         constexpr int N = decltype(n_tag)::value;
         if (!mine || c >= cc) return;
+#pragma unroll
+        for (int e = 0; e < N; ++e) bad = fmaf(sum[e], 0.f, bad);
         if (dest >= 0) store_sums<N>(out + base + c, sum);
         else store_sums<N>(a.slots + base + c, sum);
       };
-      float bad = 0.f;
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bad = fmaf(acc[m][e], 0.f, bad);
       constexpr int kPaired = sizeof(TIn) == 2 ? MT / 2 * 2 : 0;  // tiles that interleave
 #pragma unroll
       for (int m = 0; m < kPaired; m += 2) {
@@ -497,9 +497,8 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
         put(ch0 + 16 * m + 4 * g4, std::integral_constant<int, 4>{}, sum);
       }
       if ((bad != bad || s_long != 0) && mine) {
-        // an infinite or NaN sum (or, past the last channel, what LDS held), or
-        // pairs that the bytes do not number: the lane's channels again, from
-        // the segment's own pairs in order
+        // an infinite or NaN sum, or pairs that the bytes do not number: the
+        // lane's channels again, from the segment's own pairs in order
         int lo = 0, hi = np;
         while (lo < hi) {
           const int mid = (lo + hi) >> 1;

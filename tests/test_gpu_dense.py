@@ -103,6 +103,36 @@ def test_dense_infinite_and_nan_features(dtype):
     _gpu.assert_within(out[fine], ref[fine], mag[fine], dtype, "finite elements")
 
 
+def _leave_in_lds(value):
+    """Fills every compute unit's staged rows and weights with `value`."""
+    shape = dict(B=1, N=6, D=40, H=40, W=100, C=64, X=4, Y=4, Z=1)
+    sched = bp.schedule(_gpu.run_prepare(_column_coor(shape, 10), shape))
+    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    bp.forward_scheduled(torch.full((1, 6, 40, 40, 100), value, device=_gpu.DEV),
+                         torch.full((1, 6, 40, 100, 64), value, device=_gpu.DEV), sched)
+
+
+@pytest.mark.parametrize("C,dtype,out_dtype", [(52, "f32", "f32"), (36, "f32", "f32"), (100, "f32", "f32"),
+                                               (72, "f16", "f32"), (72, "f16", "f16"), (40, "f16", "f32")])
+@pytest.mark.parametrize("H,W", [(23, 61), (7, 19)])
+def test_dense_bits_do_not_depend_on_what_lds_held(H, W, C, dtype, out_dtype):
+    """Channels that do not fill their matrix tiles: the tiles' other rows read
+    past the staged features."""
+    shape = dict(B=1, N=2, D=48, H=H, W=W, C=C, X=9, Y=3, Z=1)
+    data = draw_small(np.random.default_rng(C), shape, dtype=dtype, out_dtype=out_dtype)
+    coor = _column_coor(shape, 6)
+    outs = []
+    for value in (0.0, float("nan"), float("inf")):
+        _leave_in_lds(value)
+        out, dense, _ = _forward(coor, data, shape, out_dtype)
+        assert dense, "the case is meant for the matrix cores"
+        outs.append(out)
+    ref, mag = oracle.forward_ref(data["depth"], data["feat"], coor, shape)
+    _gpu.assert_within(outs[0], ref, mag, dtype, f"C={C} {dtype} {out_dtype}")
+    for out in outs[1:]:
+        assert (out != outs[0]).sum() == 0
+
+
 def test_dense_zero_weight_of_an_infinite_feature():
     """A kept point of score 0 and an infinite feature make its cell NaN."""
     shape = dict(B=1, N=1, D=40, H=40, W=4, C=80, X=4, Y=1, Z=1)
