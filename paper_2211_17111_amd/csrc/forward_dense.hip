@@ -48,7 +48,9 @@ constexpr int kDBurst = 2;           // depth scores per pair gathered before an
 constexpr int kSegTile = 16;         // segments of one matrix tile
 constexpr int kChunkC = 256;         // channels staged at a time
 constexpr int kMaxSegs = 192;        // most segments of the index table
-constexpr int kMaxRank = 254;        // most pairs of a segment the index table numbers
+constexpr int kMaxRank = 254;        // most pixels of a strip: pairs of a segment that a byte numbers
+constexpr int kWalkGroups = kDW * 8; // most lane groups of a walk
+constexpr int kWalkStep = 4;         // pairs of a group in flight
 constexpr int kMinPoints = 18;       // points per segment from which the products pay
 // LDS of a workgroup (less the kernel's own and the allocation's granule):
 // three to a CU; two where the items are too few to need the third
@@ -125,6 +127,108 @@ __device__ __forceinline__ void store_sums(half_t* p, const float* v) {
   }
 }
 
+// An item with a pixel that meets a segment again, whose pairs are walked: lane
+// groups of one 16-byte vector of the row to a lane each take an equal range of the
+// pairs, in order, from the weights, pixels and heads in LDS.  A segment inside a
+// range is stored by its group; of one that crosses ranges each later group leaves
+// its part in LDS, over the rows, and the group it begins in adds these in order.
+// Called by the whole workgroup.
+//
+// It is bound by the chain of a group's LDS reads (pixel and weight, then row), four
+// pairs at a time.  The whole forward at 640x1600 with every point in one of nine
+// cells at random, 80 channels in float32: 119 us through k_fwd_strips, 78 us here.
+template <typename TIn, typename TOut>
+__device__ __forceinline__ void walk_item(const TIn* s_rows, const float* s_w, const uint8_t* s_px,
+                                          const uint32_t* s_heads, uint8_t* s_has, int cc, int rowvec, int np,
+                                          int nseg, int g0, int p0, int cbase, TOut* __restrict__ out,
+                                          const StripArgs& a) {
+  constexpr int V = 16 / (int)sizeof(TIn);
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int gpw = min(kWave / rowvec, kWalkGroups / kDW), groups = kDW * gpw;
+  const int lg = (int)(((float)lane + 0.5f) / (float)rowvec), vi = lane - lg * rowvec;
+  const int gi = wave * gpw + lg;
+  const int len = (int)(((float)(np + groups - 1) + 0.5f) / (float)groups);  // pairs of a range
+  const int k0 = gi * len;
+  const int mine = lg < gpw ? min(max(np - k0, 0), len) : 0;
+  // the segment of the range's first pair, or of the first head after it; lanes
+  // hold the destinations of rowvec segments from there on
+  int next = mine > 0 ? a.pair_seg[p0 + k0] : 0;
+  __builtin_amdgcn_s_waitcnt(0);
+  lds_barrier();  // (rows, weights and pixels are in LDS)
+  if (mine > 0 && (s_heads[k0 >> 5] >> (k0 & 31) & 1u) == 0) ++next;
+  int32_t dests = mine > 0 ? a.seg_dest[g0 + min(next + vi, nseg - 1)] : 0;
+  int at = 0;  // segments begun since `dests` was read
+  int32_t dest = 0;
+  bool open = false;
+  float sum[V], lead[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) sum[e] = lead[e] = 0.f;
+  auto flush = [&]() {
+    const int64_t row = dest >= 0 ? (int64_t)dest : (int64_t)~dest;
+    if (dest >= 0) {
+      if (row < a.cells) Vec<TOut, V>::store(out + row * a.C + cbase + vi * V, sum);
+    } else if (row < a.slot_cap) {
+      Vec<float, V>::store(a.slots + row * a.C + cbase + vi * V, sum);
+    }
+  };
+#pragma unroll 1
+  for (int t0 = 0; t0 < len; t0 += 32) {
+    const int k = k0 + t0;
+    const uint32_t h0 = s_heads[min(k, np - 1) >> 5], h1 = s_heads[(min(k, np - 1) >> 5) + 1];
+    const uint32_t hm = (uint32_t)((((uint64_t)h1 << 32) | h0) >> (k & 31));
+#pragma unroll 1
+    for (int t = 0; t < min(32, len - t0); t += kWalkStep) {
+      float w[kWalkStep];
+      TIn x[kWalkStep][V];
+#pragma unroll
+      for (int u = 0; u < kWalkStep; ++u) {
+        const int kk = min(k + t + u, np - 1);
+        w[u] = s_w[kk];
+        __builtin_memcpy(x[u], __builtin_assume_aligned(s_rows + s_px[kk] * cc + min(vi, rowvec - 1) * V, 16), 16);
+      }
+#pragma unroll
+      for (int u = 0; u < kWalkStep; ++u) {
+        if (t0 + t + u >= mine) break;
+        if (hm >> (t + u) & 1u) {  // a segment begins
+          if (open) flush();
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            if (!open) lead[e] = sum[e];
+            sum[e] = 0.f;
+          }
+          open = true;
+          if (at == rowvec) {
+            next += rowvec;
+            dests = a.seg_dest[g0 + min(next + vi, nseg - 1)];
+            at = 0;
+          }
+          dest = __shfl(dests, lg * rowvec + at++);
+        }
+#pragma unroll
+        for (int e = 0; e < V; ++e) sum[e] = fmaf(w[u], to_float(x[u][e]), sum[e]);
+      }
+    }
+  }
+  if (!open)
+#pragma unroll
+    for (int e = 0; e < V; ++e) lead[e] = sum[e];
+  if (lg < gpw && vi == 0) s_has[gi] = open;
+  lds_barrier();  // (the rows are no longer read)
+  float* const s_part = reinterpret_cast<float*>(const_cast<TIn*>(s_rows));
+  if (mine > 0) Vec<float, V>::store(s_part + gi * cc + vi * V, lead);
+  lds_barrier();
+  if (!open) return;
+  for (int j = gi + 1; j * len < np && j < groups; ++j) {
+    float t[V];
+    Vec<float, V>::load(s_part + j * cc + vi * V, t);
+#pragma unroll
+    for (int e = 0; e < V; ++e) sum[e] += t[e];
+    if (s_has[j]) break;
+  }
+  flush();
+}
+
 // MT: 16-channel tiles of one product; LP: pairs per thread (the item size / kDT)
 template <typename TIn, typename TOut, bool SM, int MT, int LP>
 __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ depth,
@@ -137,7 +241,9 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
   float* const s_w = reinterpret_cast<float*>(smem + s.w_off);
   uint8_t* const s_idx = reinterpret_cast<uint8_t*>(smem + s.i_off);
   double* const s_lse = reinterpret_cast<double*>(smem + s.lse_off);
-  __shared__ int32_t s_dup, s_long;  // pairs repeat a pixel; a segment has more than kMaxRank pairs
+  __shared__ uint64_t s_dup;                               // a byte per wave: its pairs repeat a pixel
+  __shared__ uint32_t s_heads[LP * kDT / 32 + 1];          // a bit per pair: first of its segment
+  __shared__ uint8_t s_has[kWalkGroups];                   // walk: a group's range has such a pair
   __shared__ uint16_t s_head[kMaxSegs];                    // each segment's first pair of the item
   __shared__ uint8_t s_first[kMaxSegs], s_last[kMaxSegs];  // and its first and last pixel
 
@@ -229,7 +335,6 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
   if constexpr (SM)
 #pragma unroll 1
     for (int i = tid; i < npix; i += kDT) s_lse[i] = a.lse[feat_row(i)];
-  if (tid == 0) s_dup = s_long = 0;
 
   // ---- depth scores of the pairs' points, kDBurst at a time, from the
   // strip's view (points outside it read nothing)
@@ -250,7 +355,8 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
   // Each pair's key: pixel | the previous pair's pixel << 8 | segment << 16 |
   // kHead | kDup; ~0 for a pair without points or outside the strip.  kDup: a
   // pair of the same segment and pixel as the pair before it (a pixel whose
-  // ray meets the cell again), which is added to that pair's weight.
+  // ray meets the cell again): the table has one entry for both, so the item's
+  // pairs are walked instead.
   constexpr uint32_t kHead = 1u << 28, kDup = 1u << 29;
   uint32_t key[LP];
 #pragma unroll
@@ -265,6 +371,15 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
                        ((ln[q] & kPairHead) ? kHead : 0u) | (dup ? kDup : 0u)
                  : ~0u;
   }
+  uint64_t dups = 0;
+#pragma unroll
+  for (int q = 0; q < LP; ++q) {
+    if (q * kWave >= span) break;
+    dups |= wave_ballot(key[q] != ~0u && (key[q] & kDup) != 0);
+    const uint64_t heads = wave_ballot((ln[q] & kPairHead) != 0);
+    if (lane < 2) s_heads[(wave * span + q * kWave) / 32 + lane] = (uint32_t)(heads >> (32 * lane));
+  }
+  if (lane == 0) reinterpret_cast<uint8_t*>(&s_dup)[wave] = dups != 0;
   // The weight of (segment, pixel) is found through a byte: 0 for none, else
   // 1 + the pair's number within its segment, whose weights lie side by side
   // in LDS.  (A table of the weights themselves takes four times the LDS, so
@@ -281,7 +396,7 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
     for (int q = 0; q < LP; ++q) {
       if (q * kWave >= span) break;
       const uint32_t k = k_first + q * kWave;
-      if ((key[q] & (kHead | kDup)) == kHead) {
+      if ((key[q] & (kHead | kDup)) == kHead) {  // (not ~0)
         const uint32_t sl = (key[q] >> 16 & 0xfffu) - (uint32_t)c0;
         if (sl < (uint32_t)cn) {
           s_head[sl] = (uint16_t)k;
@@ -313,7 +428,14 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
 #pragma unroll 1
     for (int j = kDBurst; j < n; ++j) sum += score(gather(rd0[q], j, n), lse);
     s_w[k_first + q * kWave] = sum;
-    if (n > 0 && (key[q] & kDup)) s_dup = 1;
+  }
+
+  if (s_dup != 0) {  // (uniform)
+#pragma unroll
+    for (int q = 0; q < LP; ++q)
+      if (q * kWave < span) s_idx[k_first + q * kWave] = (uint8_t)(key[q] != ~0u ? key[q] : 0u);
+    walk_item<TIn, TOut>(s_rows, s_w, s_idx, s_heads, s_has, cc, rowvec, np, nseg, g0, p0, cbase, out, a);
+    return;
   }
 
   const int i16 = lane & 15, g4 = lane >> 4;
@@ -330,31 +452,12 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
     for (int q = 0; q < LP; ++q) {
       if (q * kWave >= span) break;
       const uint32_t sl = (key[q] >> 16 & 0xfffu) - (uint32_t)c0;
-      if (sl < (uint32_t)cn && !(key[q] & kDup)) {
-        const uint32_t rank = k_first + q * kWave + 1 - s_head[sl];
-        if (rank > (uint32_t)kMaxRank) s_long = 1;
-        s_idx[sl * s.istride + (key[q] & 0xffu)] = (uint8_t)rank;
+      if (sl < (uint32_t)cn) {
+        s_idx[sl * s.istride + (key[q] & 0xffu)] = (uint8_t)(k_first + q * kWave + 1 - s_head[sl]);
       }
     }
     if (c0 == 0) __builtin_amdgcn_s_waitcnt(0);  // (the rows are in LDS)
     lds_barrier();
-    if (c0 == 0 && s_dup) {  // (uniform)
-      // the first repeated pair of a run adds the run to the pair before it
-      auto repeats = [&](int k) {
-        if (k < 1 || k >= np) return false;
-        const uint32_t l = a.pair_ln[p0 + k], b = a.pair_ln[p0 + k - 1];
-        return ((l ^ (b & kPairPixel)) & (kPairPixel | kPairHead)) == 0;
-      };
-#pragma unroll 1
-      for (int k = tid; k < np; k += kDT) {
-        if (!repeats(k) || repeats(k - 1)) continue;
-        float sum = s_w[k - 1];
-        for (int kk = k; repeats(kk); ++kk) sum += s_w[kk];
-        s_w[k - 1] = sum;
-      }
-      lds_barrier();
-    }
-
     // ---- products: channel tile as rows (M), segments as columns (N), four
     // pixels per instruction as the contraction (lane group g4 takes pixel
     // 4 step + g4); the steps no pair of the 16 segments touches are left
@@ -496,9 +599,9 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
         const float sum[4] = {acc[m][0], acc[m][1], acc[m][2], acc[m][3]};
         put(ch0 + 16 * m + 4 * g4, std::integral_constant<int, 4>{}, sum);
       }
-      if ((bad != bad || s_long != 0) && mine) {
-        // an infinite or NaN sum, or pairs that the bytes do not number: the
-        // lane's channels again, from the segment's own pairs in order
+      if (bad != bad && mine) {
+        // an infinite or NaN sum: the lane's channels again, from the segment's own
+        // pairs in order
         int lo = 0, hi = np;
         while (lo < hi) {
           const int mid = (lo + hi) >> 1;
@@ -602,8 +705,10 @@ hipError_t launch_forward_dense(const Dims& d, const StripDims& sd, bool half_in
   s.segs = (int32_t)segs;
   s.w_off = (int32_t)rows;
   s.i_off = (int32_t)(rows + a.item_pairs * 4);
-  s.lse_off = (int32_t)up(s.i_off + segs * s.istride + 64, 16);
-  const size_t lds = (size_t)(s.lse_off + lse);
+  // (a walked item keeps a byte per pair where the index table is, and at its end
+  // one float32 vector per thread from the rows on)
+  s.lse_off = (int32_t)up(s.i_off + std::max<int64_t>(segs * s.istride + 64, a.item_pairs), 16);
+  const size_t lds = (size_t)std::max<int64_t>(s.lse_off + lse, kDT * 16 / elem * 4);
   // channel tiles per product: the least padding, then the fewest passes
   const int tiles = (cc + 15) / 16;
   int mt = 2, pad = 1 << 30;
