@@ -181,6 +181,49 @@ def test_dense_infinite_and_nan_features(dtype):
     _gpu.assert_within(out[fine], ref[fine], mag[fine], dtype, "finite elements")
 
 
+# channels of whole tiles, of part of one, of two chunks; float16's tiles in pairs and alone
+@pytest.mark.parametrize("C,dtype,out_dtype", [(80, "f32", "f32"), (52, "f32", "f32"), (264, "f32", "f32"),
+                                               (48, "f16", "f32"), (72, "f16", "f16"), (128, "f16", "f32"),
+                                               (264, "f16", "f16")])
+@pytest.mark.parametrize("logits", [False, True])
+def test_dense_infinite_features_in_every_layout(C, dtype, out_dtype, logits):
+    shape = dict(B=1, N=2, D=48, H=23, W=13, C=C, X=8, Y=3, Z=1)
+    data = draw_small(np.random.default_rng(C), shape, dtype=dtype, out_dtype=out_dtype, softmax=not logits)
+    if not logits:
+        data["depth"] = np.abs(data["depth"]) + np.asarray(0.01, dtype=data["depth"].dtype)
+    coor = _column_coor(shape, 6)
+    coor.reshape(2, 48, 23, 13, 3)[0, 8:, 5, 4] = -1
+    for h, w, c, x in [(5, 4, 0, np.inf), (11, 0, C - 1, -np.inf), (22, 12, C // 2, np.nan), (0, 7, 17, np.inf)]:
+        data["feat"][0, 0, h, w, c] = x
+    sched = bp.schedule(_gpu.run_prepare(coor, shape))
+    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
+                    else (bp.forward_scheduled, oracle.forward_ref))
+    out = forward(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched, out_dtype=_gpu.torch_dtype(out_dtype))
+    out = out.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        want, mag = ref(data["depth"], data["feat"], coor, shape)
+    fine = np.isfinite(want)
+    assert (~fine).sum() > 8 and fine.sum() > 8
+    assert np.array_equal(out[~fine].astype(np.float64), want[~fine], equal_nan=True)
+    _gpu.assert_within(out[fine], want[fine], mag[fine], dtype, "finite elements")
+
+
+def test_dense_infinite_features_stay_fast():
+    """A feature map of infinities takes at most 4 times as long as a finite one
+    (640x1600: 1.6, and 1.5 with one infinity; with a chain of global loads per pair
+    and channel: 38)."""
+    shape = dict(B=1, N=6, D=118, H=40, W=100, C=80, X=40, Y=8, Z=1)
+    sched = bp.schedule(_gpu.run_prepare(_column_coor(shape, 4), shape))
+    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    depth = torch.rand((1, 6, 118, 40, 100), device=_gpu.DEV)
+    feat = torch.randn((1, 6, 40, 100, 80), device=_gpu.DEV)
+    finite = _fastest(lambda: bp.forward_scheduled(depth, feat, sched))
+    assert _fastest(lambda: bp.forward_scheduled(depth, feat / 0, sched)) < 4 * finite
+    feat[0, :, 7::16, 5::16, 3] = float("inf")
+    assert _fastest(lambda: bp.forward_scheduled(depth, feat, sched)) < 4 * finite
+
+
 def _leave_in_lds(value):
     """Fills every compute unit's staged rows and weights with `value`."""
     shape = dict(B=1, N=6, D=40, H=40, W=100, C=64, X=4, Y=4, Z=1)
