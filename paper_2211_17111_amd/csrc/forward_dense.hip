@@ -371,15 +371,14 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
                        ((ln[q] & kPairHead) ? kHead : 0u) | (dup ? kDup : 0u)
                  : ~0u;
   }
-  uint64_t dups = 0;
+  bool dup = false;
 #pragma unroll
   for (int q = 0; q < LP; ++q) {
     if (q * kWave >= span) break;
-    dups |= wave_ballot(key[q] != ~0u && (key[q] & kDup) != 0);
-    const uint64_t heads = wave_ballot((ln[q] & kPairHead) != 0);
-    if (lane < 2) s_heads[(wave * span + q * kWave) / 32 + lane] = (uint32_t)(heads >> (32 * lane));
+    dup |= key[q] != ~0u && (key[q] & kDup) != 0;
   }
-  if (lane == 0) reinterpret_cast<uint8_t*>(&s_dup)[wave] = dups != 0;
+  const bool dups = wave_ballot(dup) != 0;
+  if (lane == 0) reinterpret_cast<uint8_t*>(&s_dup)[wave] = dups;
   // The weight of (segment, pixel) is found through a byte: 0 for none, else
   // 1 + the pair's number within its segment, whose weights lie side by side
   // in LDS.  (A table of the weights themselves takes four times the LDS, so
@@ -430,10 +429,14 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
     s_w[k_first + q * kWave] = sum;
   }
 
-  if (s_dup != 0) {  // (uniform)
+  if (__builtin_expect(s_dup != 0, 0)) {  // (uniform)
 #pragma unroll
-    for (int q = 0; q < LP; ++q)
-      if (q * kWave < span) s_idx[k_first + q * kWave] = (uint8_t)(key[q] != ~0u ? key[q] : 0u);
+    for (int q = 0; q < LP; ++q) {
+      if (q * kWave >= span) break;
+      s_idx[k_first + q * kWave] = (uint8_t)(key[q] != ~0u ? key[q] : 0u);
+      const uint64_t heads = wave_ballot((ln[q] & kPairHead) != 0);
+      if (lane < 2) s_heads[(wave * span + q * kWave) / 32 + lane] = (uint32_t)(heads >> (32 * lane));
+    }
     walk_item<TIn, TOut>(s_rows, s_w, s_idx, s_heads, s_has, cc, rowvec, np, nseg, g0, p0, cbase, out, a);
     return;
   }
@@ -592,7 +595,7 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
 #pragma unroll
         for (int e = 0; e < 4; ++e) bad = c < cc ? fmaf(acc[m][e], 0.f, bad) : bad;
       }
-      if (bad != bad && mine) {
+      if (__builtin_expect(bad != bad && mine, 0)) {
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[m] = float4_t{0.f, 0.f, 0.f, 0.f};
         const uint8_t* const idx = s_idx + (seg - c0) * s.istride;
