@@ -45,6 +45,7 @@ namespace {
 constexpr int kDT = 512;             // threads of a workgroup
 constexpr int kDW = kDT / kWave;     // 8 waves
 constexpr int kDBurst = 2;           // depth scores per pair gathered before any is summed
+constexpr int kDTail = 4;            // and at a time after these
 constexpr int kSegTile = 16;         // segments of one matrix tile
 constexpr int kChunkC = 256;         // channels staged at a time
 constexpr int kMaxSegs = 192;        // most segments of the index table
@@ -52,6 +53,8 @@ constexpr int kMaxRank = 254;        // most pixels of a strip: pairs of a segme
 constexpr int kWalkGroups = kDW * 8; // most lane groups of a walk
 constexpr int kWalkStep = 4;         // pairs of a group in flight
 constexpr int kMinPoints = 18;       // points per segment from which the products pay
+constexpr double kFinePoints = 4;    // points per expected pair from which bins are fine
+constexpr double kMinFill = 0.16;    // share of the table's entries with a pair from which products pay there
 // LDS of a workgroup (less the kernel's own and the allocation's granule):
 // three to a CU; two where the items are too few to need the third
 constexpr int kDenseLds = 160 * 1024 / 3 - 2304;
@@ -424,8 +427,17 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
 #pragma unroll
     for (int j = 1; j < kDBurst; ++j)
       if (j < n) sum += score(dv[q][j], lse);
+    // (longer runs come from bins finer than the cells: one score at a time, two
+    // samples at 16x88 pixels with 472 bins took 56 us, four at a time 49 us)
 #pragma unroll 1
-    for (int j = kDBurst; j < n; ++j) sum += score(gather(rd0[q], j, n), lse);
+    for (int j0 = kDBurst; j0 < n; j0 += kDTail) {
+      TIn x[kDTail];
+#pragma unroll
+      for (int j = 0; j < kDTail; ++j) x[j] = gather(rd0[q], j0 + j, n);
+#pragma unroll
+      for (int j = 0; j < kDTail; ++j)
+        if (j0 + j < n) sum += score(x[j], lse);
+    }
     s_w[k_first + q * kWave] = sum;
   }
 
@@ -676,6 +688,21 @@ hipError_t run_tiles(const Dims& d, const DenseArgs& s, int mt, size_t lds, cons
 // channels) 289 / 58 us; 14.5 (eight samples at 256x704) 49.7 / 48.1 us
 // in float32 but 45.4 / 47.3 us in float16; 10 (256x704) 14.2 / 17.4 us; 2.7
 // (voxels) 74.4 / 74.3 us.
+//
+// The products' cost goes with the table's entries, of which only those with a
+// pair do any good, and where bins are finer than cells a segment of many points
+// has few pairs.  The pairs are not known here; but a ray meets about a third of X
+// + Y cells (0.34 of them at 4x100 pixels and 944 bins, 0.16 at 640x1600, where the
+// grid's height cuts the rays off), so a pixel is taken to have no more pairs.  Walk
+// against products, 80 channels in float32, at points per expected pair and
+// share of the entries: 9.7 and 0.05 (four samples at 2x100 pixels, 944 bins, 128 x 128
+// cells) 39 / 81 us; 19 and 0.15 (4x100, 64 x 64 cells) 45 / 77 us; 19 and 0.04
+// (1x100) 22 / 29 us; 9.7 and 0.14 (one sample at 4x100, 472 bins) 15.7 / 17.8 us.
+// But 5.4 and 0.66 (40x100, 472 bins) 52 / 48 us; 5.7 and 0.25 (16x44) 18.5 / 16.5
+// us; 4.8 and 0.22 (eight samples at 4x352, 128 x 128 cells) 193 / 170 us, and
+// 213 / 113 us in float16.  Between them the types differ: 9.7 and 0.13 (2x352, 944
+// bins) 143 / 174 us, and 147 / 119 us in float16, which the rule gives up.
+//
 // The index numbers a segment's pairs in a byte, so strips have at most
 // kMaxRank pixels (narrower strips than those of 32 channels and fewer).  A
 // view's depth scores and a strip's rows are reached by 32-bit byte offsets.
@@ -683,8 +710,11 @@ bool dense_forward_ok(const Dims& d, const StripDims& sd, bool half_in, int32_t 
                       int32_t n_slots) {
   const int64_t elem = half_in ? 2 : 4;
   const int64_t view_bytes = d.D * d.hw * elem, strip_bytes = (sd.bh + 1) * d.W * d.C * elem;
-  return sd.pixels <= kMaxRank && view_bytes < ((int64_t)1 << 31) && strip_bytes < ((int64_t)1 << 31) &&
-         n_valid >= (int64_t)kMinPoints * ((int64_t)n_intervals + n_slots);
+  const int64_t segs = (int64_t)n_intervals + n_slots;
+  const double pairs = (double)(d.X + d.Y) / 3 * (double)d.rows;  // most that are expected
+  const bool sparse = n_valid > kFinePoints * pairs && pairs < kMinFill * (double)segs * (double)sd.pixels;
+  return !sparse && sd.pixels <= kMaxRank && view_bytes < ((int64_t)1 << 31) && strip_bytes < ((int64_t)1 << 31) &&
+         n_valid >= kMinPoints * segs;
 }
 
 hipError_t launch_forward_dense(const Dims& d, const StripDims& sd, bool half_in, bool half_out,

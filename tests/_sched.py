@@ -8,7 +8,11 @@ schedule can be checked bit for bit.
 
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
+
+from paper_2211_17111_amd import bevpool as bp
 
 ALIGN = 256
 ITEM_PAIRS = 2048
@@ -196,3 +200,15 @@ def derive(plan: dict, shape, shares: int = 1) -> dict:
         item_seg0=np.r_[item_seg0, nsegs].astype(np.int64), seg_dest=seg_dest,
         comb_cell=comb_cell, comb_slot0=comb_slot0, empty=empty,
         bp_cell=bp_cell, bp_dn=bp_dn, pix_pair0=pix_pair0, share_item0=share_item0.astype(np.int64))
+
+
+def dense_forward(shape, n_valid: int, n_occ: int, n_slots: int, half: bool = False) -> bool:
+    """Whether the library pools such a schedule on the matrix cores: its own
+    rule (a host function), for features of whole 16-byte vectors."""
+    rule = bp.load_library()["_ZN7bevpool16dense_forward_okERKNS_4DimsERKNS_9StripDimsEbiii"]
+    rule.restype = ctypes.c_bool
+    rule.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_bool] + [ctypes.c_int32] * 3
+    B, N, D, H, W, C, X, Y, Z = (shape[k] for k in "BNDHWCXYZ")
+    dims = [B, N, D, H, W, C, X, Y, Z, B * N * D * H * W, B * N * H * W, B * Z * Y * X, D * H * W, H * W]
+    strips = list(strip_dims(shape)[k] for k in ("bh", "bw", "nhb", "nwb", "strips", "pixels"))
+    return rule((ctypes.c_int64 * 14)(*dims), (ctypes.c_int64 * 6)(*strips), half, n_valid, n_occ, n_slots)

@@ -11,6 +11,7 @@ import pytest
 import torch
 
 import _gpu
+import _sched
 import oracle
 from paper_2211_17111_amd import bevpool as bp
 from workloads import draw_small, random_coor
@@ -63,6 +64,28 @@ def test_dense_strips(H, W, D, run, X):
     assert dense, "the case is meant for the matrix cores"
     ref, mag = oracle.forward_ref(data["depth"], data["feat"], coor, shape)
     _gpu.assert_within(out, ref, mag, "f32", f"{H}x{W} D={D}")
+
+
+# runs of bins around the number of depth scores taken at a time; 41 rows (segments
+# that see most of a strip's pixels) or 2 (few of them: not on the matrix cores)
+@pytest.mark.parametrize("H,dtype,C,run", [(41, dtype, C, run) for dtype, C in (("f32", 80), ("f16", 72))
+                                           for run in (1, 2, 3, 5, 6, 7, 10, 11, 14, 40)]
+                         + [(2, "f32", 80, run) for run in (6, 7, 10, 11, 40)])
+@pytest.mark.parametrize("logits", [False, True])
+def test_dense_points_per_pair(H, dtype, C, run, logits):
+    shape = dict(B=1, N=2, D=5 * run, H=H, W=20 if H > 2 else 40, C=C, X=3 if H > 2 else 8, Y=2, Z=1)
+    data = draw_small(np.random.default_rng(run), shape, dtype=dtype, softmax=not logits)
+    coor = _column_coor(shape, run)
+    if H == 2:
+        coor.reshape(2, -1, 2, 40, 3)[:, 3 * run:] = -1    # three pairs to a pixel
+    sched = bp.schedule(_gpu.run_prepare(coor, shape))
+    counts = (sched.plan.n_valid, sched.plan.n_intervals, sched.n_slots)
+    assert _sched.dense_forward(shape, *counts, half=dtype == "f16") == (H > 2), counts
+    forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
+                    else (bp.forward_scheduled, oracle.forward_ref))
+    out = forward(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched)
+    want, mag = ref(data["depth"], data["feat"], coor, shape)
+    _gpu.assert_within(out.cpu().numpy(), want, mag, dtype, f"run={run} H={H}")
 
 
 # A pixel meets a cell again and again (runs of pairs of one segment and pixel),
