@@ -529,6 +529,10 @@ size_t backward_workspace_bytes(const Dims& d) { return sizeof(int32_t) * (size_
 // 43.4 us (eight samples at 256x704).  Float16 rows are short enough that a second
 // load costs more: 113 / 124 us (four frames at 640x1760; 10 channels, a vector of
 // 8 and a tail in groups of 8 lanes: 107 us, not worth its instances).
+// Float32 rows of 8 and 16 channels take 4: as one or two lanes a pixel takes its
+// depth bins or pairs one or two at a time.  8 / 4 at 640x1600 from the plan: 126 /
+// 87 us (8 channels) and 89 / 57 us (16), scheduled 107 / 54 and 57 / 33 us; at 24
+// channels both give groups of 4 lanes or more, and 8 is the faster.
 template <typename TIn, typename TG>
 hipError_t dispatch_channels(const Dims& d, bool al, const void* grad_out, const void* depth, const void* feat,
                              const PixArgs& a, void* grad_depth, void* grad_feat, hipStream_t stream) {
@@ -543,7 +547,8 @@ hipError_t dispatch_channels(const Dims& d, bool al, const void* grad_out, const
     BWD_FILL(6, 32);
   }
 #undef BWD_FILL
-  if (al && d.C % 8 == 0)
+  const bool narrow = sizeof(TIn) == 4 && d.C <= 16;
+  if (al && d.C % 8 == 0 && !narrow)
     return run_pixels_nv<TIn, TG, 8>(d, grad_out, depth, feat, a, grad_depth, grad_feat, stream);
   if constexpr (sizeof(TIn) == 4)
     if (al && d.C % 4 == 0)

@@ -85,6 +85,15 @@ def test_channel_layouts(C, dtype, out_dtype, B, H, W, D, path):
     _gpu.assert_within(gf.float().cpu().numpy(), rgf, mgf, dtype, f"C={C} {path} grad_feat")
 
 
+# rows of one or two 32-byte vectors, and those around them
+@pytest.mark.parametrize("C", [4, 8, 12, 16, 24])
+@pytest.mark.parametrize("dtype,out_dtype", [("f32", "f32"), ("f16", "f32")])
+@pytest.mark.parametrize("B,H,W,D", [(1, 3, 7, 20), (1, 73, 225, 4)])
+@pytest.mark.parametrize("path", ["plan", "scheduled"])
+def test_narrow_rows(C, dtype, out_dtype, B, H, W, D, path):
+    test_channel_layouts(C, dtype, out_dtype, B, H, W, D, path)
+
+
 @pytest.mark.parametrize("path", ["plan", "scheduled"])
 def test_gradient_of_a_gibibyte(path):
     """grad_out of 1 GiB: its rows lie beyond what the 32-bit offsets address."""
