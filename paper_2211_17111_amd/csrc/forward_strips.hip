@@ -82,6 +82,15 @@ static_assert(kItemPairsBig <= 65536, "segment index fits 16 bits");
 static_assert(2 * buf_bytes(kItemPairsBig) + 16 * 1024 <= 160 * 1024, "two big item buffers fit LDS");
 static_assert(kShareItems <= kHdrCache, "a share's item headers fit the cache");
 
+// header_ok, one count after another.  With the counts tested together the instances
+// from float16 logits, which spill registers, come out slower: 16 channels at
+// 640x1600 113 / 119 us.
+__device__ __forceinline__ bool header_ok_in_turn(const StripArgs& a) {
+  const int32_t* hdr = a.hdr;
+  return hdr[kHdrOcc] == a.n_occ && hdr[kHdrOccFound] == a.n_occ && hdr[kHdrValid] == a.n_valid &&
+         hdr[kHdrSlots] == a.n_slots && hdr[kHdrItemPairs] == a.item_pairs;
+}
+
 struct PairRec {
   float w;      // summed depth score
   uint32_t ps;  // row offset (local pixel * vectors per row) | segment << 19 | kRecHead
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(kNT) void k_fwd_strips(const TIn* __restrict__ dept
   // (the share bounds are read with the counts; used only if they apply)
   const int32_t sh_lo = a.share_item0[min(w_idx, kMaxShares)];
   const int32_t sh_hi = a.share_item0[min(w_idx + 1, kMaxShares)];
-  if (!header_ok(a)) return;  // (uniform; k_fwd_combine writes NaN everywhere)
+  if (!header_ok_in_turn(a)) return;  // (uniform; k_fwd_combine writes NaN everywhere)
   const int32_t n_items = min(hdr[kHdrItems], a.items_cap);
   const int32_t n_pairs = min(hdr[kHdrPairs], a.n_valid);
   const int32_t n_segs = min(hdr[kHdrSegs], a.n_valid);
