@@ -195,9 +195,6 @@ struct RowReg {
     if constexpr (kTails > 0) get<kTails * (int)sizeof(T)>(kLead, r, tail);
   }
 };
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
 // grad_out as a buffer: below 1 GiB, so that the offsets of "no pair" and of
 // "no channel", alone or added, lie past its end
 constexpr int64_t kBufferBytes = (int64_t)1 << 30;

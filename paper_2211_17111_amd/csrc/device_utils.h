@@ -1,4 +1,4 @@
-// Wave-level helpers for CDNA (64-lane wavefronts).
+// Device helpers for CDNA (64-lane wavefronts).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -62,6 +62,33 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* lds, int* total)
   if (LDS_ONLY) lds_barrier(); else __syncthreads();
   *total = tot;
   return off + inc - v;
+}
+
+// 16 bytes per lane from memory straight into LDS (global_load_lds_dwordx4):
+// lane i of the wave writes at lds + 16 i, lds being the same for the wave.
+// (A plain device function: inside the kernel template the builtin keeps the
+// host pass from emitting the kernel's launch stub.)
+__device__ __forceinline__ void global_to_lds16(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// A range of memory for buffer loads: a byte offset past its end reads nothing
+// and gives 0.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+
+// Division of numbers below 2^31 by a divisor the host knows: at most one too
+// much from the rounded-up reciprocal, corrected.
+struct Divisor {
+  uint32_t d, m;
+  __device__ __forceinline__ uint32_t div(uint32_t n) const {
+    const uint32_t q = d == 1 ? n : (uint32_t)(((uint64_t)n * m) >> 32);
+    return q * d > n ? q - 1 : q;
+  }
+};
+inline Divisor divisor(int64_t d) {
+  return Divisor{(uint32_t)d, (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d)};
 }
 
 }  // namespace bevpool

@@ -61,19 +61,6 @@ constexpr int kDenseLds = 160 * 1024 / 3 - 2304;
 constexpr int kDenseLdsFew = 160 * 1024 / 2 - 2304;
 constexpr int kFewItems = 512;
 
-// Division of numbers below 2^31 by a divisor the host knows: at most one too
-// much from the rounded-up reciprocal, corrected.
-struct Divisor {
-  uint32_t d, m;
-  __device__ __forceinline__ int32_t div(int32_t n) const {
-    const uint32_t q = d == 1 ? (uint32_t)n : (uint32_t)(((uint64_t)(uint32_t)n * m) >> 32);
-    return (int32_t)(q * d > (uint32_t)n ? q - 1 : q);
-  }
-};
-Divisor divisor(int64_t d) {
-  return Divisor{(uint32_t)d, (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d)};
-}
-
 struct DenseArgs {
   int32_t segs;      // segments the index table holds (a multiple of kSegTile)
   int32_t istride;   // bytes per segment of the index table
@@ -91,25 +78,17 @@ __device__ __forceinline__ int32_t uniform_load(const int32_t* p) {
   return *(const __attribute__((address_space(4))) int32_t*)p;
 }
 
-__device__ __forceinline__ void global_to_lds16(const void* g, void* lds) {
-  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
-}
-
 __device__ __forceinline__ float4_t mfma_16x16x4(float a, float b, float4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Loads from a range of memory: a byte offset past its end reads nothing and
-// gives 0.
+// A depth score or schedule entry from a range of memory
 template <typename T>
 __device__ __forceinline__ T range_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   if constexpr (sizeof(T) == 4)
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
   else
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0));
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t range_of(const void* p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
 // N consecutive sums to a float32 or float16 destination, 16 (or 8) bytes at a time
@@ -278,9 +257,9 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
        (int)(p0 + np > n_pairs) | (int)(g0 < 0) | (int)(nseg < 1) | (int)(nseg > np) |
        (int)(g0 + nseg > n_segs)) != 0)
     return;
-  const int32_t bn = s.sper.div(strip);
+  const int32_t bn = (int32_t)s.sper.div((uint32_t)strip);
   const int32_t sr = strip - bn * (int32_t)s.sper.d;
-  const int32_t hb = s.nwb.div(sr);
+  const int32_t hb = (int32_t)s.nwb.div((uint32_t)sr);
   const int32_t h0 = hb * a.bh, w0 = (sr - hb * a.nwb) * a.bw;
   const int32_t bws = min(a.bw, a.W - w0);
   const int32_t npix = min(a.bh, a.H - h0) * bws;
@@ -295,8 +274,8 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
   // 64 (past the item's end they read as pairs of no points)
   const int span = (np + kDT - 1) / kDT * kWave;
   const uint32_t k_first = (uint32_t)(wave * span + lane);
-  const __amdgpu_buffer_rsrc_t r_rd0 = range_of(a.pair_rd0 + p0, np * 4), r_ln = range_of(a.pair_ln + p0, np * 4),
-                               r_sg = range_of(a.pair_seg + p0, np * 2);
+  const __amdgpu_buffer_rsrc_t r_rd0 = buffer_of(a.pair_rd0 + p0, np * 4), r_ln = buffer_of(a.pair_ln + p0, np * 4),
+                               r_sg = buffer_of(a.pair_seg + p0, np * 2);
   uint32_t rd0[LP], ln[LP], sg[LP];
 #pragma unroll
   for (int q = 0; q < LP; ++q) {
@@ -342,7 +321,7 @@ __global__ __launch_bounds__(kDT, 6) void k_fwd_dense(const TIn* __restrict__ de
   // ---- depth scores of the pairs' points, kDBurst at a time, from the
   // strip's view (points outside it read nothing)
   const int32_t vbase = bn * a.dhw;
-  const __amdgpu_buffer_rsrc_t r_view = range_of(depth + (int64_t)vbase, s.view_bytes);
+  const __amdgpu_buffer_rsrc_t r_view = buffer_of(depth + (int64_t)vbase, s.view_bytes);
   auto gather = [&](uint32_t rd, int j, int n) -> TIn {
     uint32_t off = (rd - (uint32_t)vbase + (uint32_t)j * (uint32_t)a.hw32) * (uint32_t)sizeof(TIn);
     if (j > 0) off = j < n ? off : ~0u;
@@ -670,7 +649,6 @@ template <typename TIn, typename TOut, bool SM>
 hipError_t run_tiles(const Dims& d, const DenseArgs& s, int mt, size_t lds, const void* depth, const void* feat,
                      const StripArgs& a, void* out, hipStream_t stream) {
   switch (mt) {
-    case 1:
     case 2: return run<TIn, TOut, SM, 2>(d, s, lds, depth, feat, a, out, stream);
     case 3: return run<TIn, TOut, SM, 3>(d, s, lds, depth, feat, a, out, stream);
     case 4: return run<TIn, TOut, SM, 4>(d, s, lds, depth, feat, a, out, stream);

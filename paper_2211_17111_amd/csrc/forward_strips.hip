@@ -50,14 +50,6 @@ namespace bevpool {
 
 namespace {
 
-// 16 bytes per lane from memory straight into LDS (global_load_lds_dwordx4):
-// lane i of the wave writes at lds + 16 i, lds being the same for the wave.
-// (A plain device function: inside the kernel template the builtin keeps the
-// host pass from emitting the kernel's launch stub.)
-__device__ __forceinline__ void global_to_lds16(const void* g, void* lds) {
-  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
-}
-
 // One workgroup per CU: kLoadWaves waves fetch the next item into one LDS
 // buffer while the other waves walk the current item in the other.
 constexpr int kNT = 1024;

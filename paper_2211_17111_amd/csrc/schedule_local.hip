@@ -30,19 +30,6 @@ constexpr int kLBuckets = 256;             // most pixels of a strip: digits of 
 constexpr int kLItems = kMaxShares + kLocalPoints / kItemPairs + 2;  // items of one strip
 static_assert(kLocalPoints % kLT == 0, "whole rounds");
 
-// Division of numbers below 2^31 by a divisor the host knows: at most one too
-// much from the rounded-up reciprocal, corrected.
-struct Divisor {
-  uint32_t d, m;
-  __device__ __forceinline__ uint32_t div(uint32_t n) const {
-    const uint32_t q = d == 1 ? n : (uint32_t)(((uint64_t)n * m) >> 32);
-    return q * d > n ? q - 1 : q;
-  }
-};
-Divisor divisor(int64_t d) {
-  return Divisor{(uint32_t)d, (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d)};
-}
-
 struct LGeom {
   Divisor by_view, by_hw, by_w, by_bh, by_bw;  // D * H * W, H * W, W, bh, bw
   int32_t N, D, H, W, bh, bw, nhb, nwb, strips;
@@ -77,7 +64,7 @@ __device__ __forceinline__ int32_t strip_of_block(int32_t strips) {
 // One stable counting pass over the n elements held by a workgroup in the
 // wave-round layout (element e = wave * span + round * 64 + lane): returns in
 // dest[r] each element's position in the order of digit, then element.  cnt
-// is kLW x NB ints of LDS and match kLW x NB x 2 words (NB >= the digits); after
+// is kLW x kLBuckets ints of LDS and match kLW x kLBuckets x 2 words; after
 // the pass cnt[0][d] holds the first position of digit d.  Every thread of
 // the block must call it.
 //
@@ -88,15 +75,14 @@ __device__ __forceinline__ int32_t strip_of_block(int32_t strips) {
 // adds the digit's count to the wave's counter with a returning LDS add; the
 // adds of all rounds are issued before any result is used, and each returns
 // the count of that digit in the wave's earlier rounds.
-template <int NB>
 __device__ __forceinline__ void local_ranks(const uint32_t (&key)[kLR], int shift, int bits, int n, int span,
-                                            int32_t (*cnt)[NB], uint32_t (*match)[NB][2],
+                                            int32_t (*cnt)[kLBuckets], uint32_t (*match)[kLBuckets][2],
                                             int32_t* s_scan, int32_t (&dest)[kLR]) {
   const int lane = lane_id();
   const int wid = threadIdx.x / kWave;
   const int t = threadIdx.x;
-  for (int i = t; i < kLW * NB; i += kLT) (&cnt[0][0])[i] = 0;
-  for (int i = t; i < kLW * NB * 2; i += kLT) (&match[0][0][0])[i] = 0u;
+  for (int i = t; i < kLW * kLBuckets; i += kLT) (&cnt[0][0])[i] = 0;
+  for (int i = t; i < kLW * kLBuckets * 2; i += kLT) (&match[0][0][0])[i] = 0u;
   __syncthreads();
   const int rounds = span / kWave;
   const uint32_t mask = (1u << bits) - 1u;
@@ -133,7 +119,7 @@ __device__ __forceinline__ void local_ranks(const uint32_t (&key)[kLR], int shif
   __syncthreads();
   // digit t: each wave's offset within the digit, and the digit's count
   int tot = 0;
-  if (t < NB) {
+  if (t < kLBuckets) {
 #pragma unroll
     for (int w = 0; w < kLW; ++w) {
       const int x = cnt[w][t];
@@ -143,7 +129,7 @@ __device__ __forceinline__ void local_ranks(const uint32_t (&key)[kLR], int shif
   }
   int total;
   const int start = block_exclusive_scan<kLT>(tot, s_scan, &total);
-  if (t < NB) {
+  if (t < kLBuckets) {
 #pragma unroll
     for (int w = 0; w < kLW; ++w) cnt[w][t] += start;
   }
@@ -295,7 +281,7 @@ __global__ __launch_bounds__(kLT) void k_ls_strips(const int32_t* __restrict__ m
         const int e = wid * span + r * kWave + lane;
         key[r] = e < n ? sa[e] : 0u;
       }
-      local_ranks<kLBuckets>(key, shift, bits, n, span, cnt, match, s_scan, dest);
+      local_ranks(key, shift, bits, n, span, cnt, match, s_scan, dest);
 #pragma unroll
       for (int r = 0; r < kLR; ++r) {
         if (r * kWave >= span) continue;
@@ -659,7 +645,7 @@ __global__ __launch_bounds__(kLT) void k_ls_emit(
   }
   // pixel-major pairs: a stable pass by local pixel
   int32_t dest[kLR];
-  local_ranks<kLBuckets>(key, g.d_bits, g.lp_bits, np, span, cnt, match, s_scan, dest);
+  local_ranks(key, g.d_bits, g.lp_bits, np, span, cnt, match, s_scan, dest);
 #pragma unroll
   for (int r = 0; r < kLR; ++r) {
     if (r * kWave >= span) continue;
