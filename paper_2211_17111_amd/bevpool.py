@@ -154,12 +154,18 @@ def _ptr(x) -> int | None:
     return None if x is None else int(x)
 
 
+# The raw handle of a device's current stream, where this torch has that private
+# function (a torch.cuda.Stream object costs five times as much).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
     if stream is None:
         if not torch.cuda.is_available():
             return None
-        # (the raw handle: a torch.cuda.Stream object costs five times as much)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

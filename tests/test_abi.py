@@ -280,3 +280,18 @@ def test_geometry_validation():
     assert g(f=dict(lo=(float("nan"), -8.0, -5.0))) == EINVAL
     assert g(f=dict(depth_start=float("inf"))) == EINVAL
 
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_without_torchs_private_function(monkeypatch, private):
+    """The current stream's handle comes from the public call where torch lacks
+    the raw one."""
+    class Stream:
+        cuda_stream = 0x77
+
+    monkeypatch.setattr(bp.torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(bp.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(bp.torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(bp, "_raw_stream", (lambda device: 0x70 + device) if private else None)
+    assert bp._stream(None) == (0x73 if private else 0x77)
+    assert bp._stream(0x55) == 0x55
