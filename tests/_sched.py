@@ -212,3 +212,19 @@ def dense_forward(shape, n_valid: int, n_occ: int, n_slots: int, half: bool = Fa
     dims = [B, N, D, H, W, C, X, Y, Z, B * N * D * H * W, B * N * H * W, B * Z * Y * X, D * H * W, H * W]
     strips = list(strip_dims(shape)[k] for k in ("bh", "bw", "nhb", "nwb", "strips", "pixels"))
     return rule((ctypes.c_int64 * 14)(*dims), (ctypes.c_int64 * 6)(*strips), half, n_valid, n_occ, n_slots)
+
+
+def dense_table(shape, n_valid: int, half: bool, logits: bool, workgroups: int) -> int:
+    """Segments that the matrix form's index table holds: what a third of a compute
+    unit's LDS (with few items half of it) leaves beside the strip's rows, the
+    pairs' weights and the log-sum-exps."""
+    def up(v, m):
+        return -(-v // m) * m
+
+    sd = strip_dims(shape)
+    npad = up(sd["pixels"], 16)
+    rows = up(npad * min(shape["C"], 256) * (2 if half else 4), 1024)
+    lse = up(npad * 8, 16) if logits else 0
+    budget = 160 * 1024 // (2 if sd["strips"] + workgroups <= 512 else 3) - 2304
+    segs = (budget - rows - lse - 64 - 4 * item_pairs(n_valid)) // (npad + 4) // 16 * 16
+    return max(16, min(192, segs))

@@ -18,7 +18,16 @@ from workloads import draw_small, random_coor
 
 pytestmark = pytest.mark.gpu
 
-MIN_POINTS = 18  # points per segment from which the forward multiplies
+
+def _dense(sched, half):
+    """Whether the library pools the schedule on the matrix cores."""
+    return _sched.dense_forward(sched.plan.shape, sched.plan.n_valid, sched.plan.n_intervals, sched.n_slots, half)
+
+
+def _roomy(shape):
+    """The grid with empty cells along x, at least as many as a pixel has bins: the
+    rule then expects a pair per bin, so few cells do not make the bins fine."""
+    return dict(shape, X=max(shape["X"], shape["D"]))
 
 
 def _column_coor(shape, run):
@@ -31,7 +40,7 @@ def _column_coor(shape, run):
 
 def _forward(coor, data, shape, out_dtype):
     sched = bp.schedule(_gpu.run_prepare(coor, shape))
-    dense = sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    dense = _dense(sched, data["feat"].dtype == np.float16)
     out = bp.forward_scheduled(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched,
                                out_dtype=_gpu.torch_dtype(out_dtype))
     return out.cpu().numpy(), dense, sched
@@ -53,13 +62,14 @@ def test_dense_channels(C, dtype, out_dtype):
     _gpu.assert_within(out, ref, mag, dtype, f"C={C} {dtype} {out_dtype}")
 
 
-# (3, 17) one image row of odd pixels; a strip whose segments outnumber the
-# index table (many cells, short runs over many rows); one point in all
+# strips of 3 x 17 and 5 x 7 pixels, of 17 x 6 in several bands, of 16 x 6 in
+# several columns; runs of a whole ray down to single bins
 @pytest.mark.parametrize("H,W,D,run,X", [(3, 17, 70, 30, 3), (5, 7, 118, 59, 5), (40, 6, 112, 1, 40), (16, 44, 59, 4, 16)])
 def test_dense_strips(H, W, D, run, X):
     shape = dict(B=1, N=3, D=D, H=H, W=W, C=80, X=X, Y=4, Z=1)
     data = draw_small(np.random.default_rng(H), shape)
     coor = _column_coor(shape, run)
+    shape = _roomy(shape)
     out, dense, _ = _forward(coor, data, shape, "f32")
     assert dense, "the case is meant for the matrix cores"
     ref, mag = oracle.forward_ref(data["depth"], data["feat"], coor, shape)
@@ -79,8 +89,7 @@ def test_dense_points_per_pair(H, dtype, C, run, logits):
     if H == 2:
         coor.reshape(2, -1, 2, 40, 3)[:, 3 * run:] = -1    # three pairs to a pixel
     sched = bp.schedule(_gpu.run_prepare(coor, shape))
-    counts = (sched.plan.n_valid, sched.plan.n_intervals, sched.n_slots)
-    assert _sched.dense_forward(shape, *counts, half=dtype == "f16") == (H > 2), counts
+    assert _dense(sched, dtype == "f16") == (H > 2)
     forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
                     else (bp.forward_scheduled, oracle.forward_ref))
     out = forward(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched)
@@ -96,6 +105,7 @@ def test_dense_repeated_pixels(X, Y, D):
     rng = np.random.default_rng(D)
     data = draw_small(rng, shape)
     coor = random_coor(rng, shape, spread=1)
+    shape = _roomy(shape)
     out, dense, _ = _forward(coor, data, shape, "f32")
     assert dense, "the case is meant for the matrix cores"
     ref, mag = oracle.forward_ref(data["depth"], data["feat"], coor, shape)
@@ -122,8 +132,9 @@ def test_dense_walked_items(X, Y, D, H, W, C, dtype, out_dtype, logits):
     shape = dict(B=1, N=2, D=D, H=H, W=W, C=C, X=X, Y=Y, Z=1)
     data = draw_small(np.random.default_rng(C + D), shape, dtype=dtype, out_dtype=out_dtype, softmax=not logits)
     coor = _alternate_coor(shape)
+    shape = _roomy(shape)
     sched = bp.schedule(_gpu.run_prepare(coor, shape))
-    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    assert _dense(sched, dtype == "f16")
     forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
                     else (bp.forward_scheduled, oracle.forward_ref))
     args = (_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched)
@@ -139,6 +150,7 @@ def test_dense_walked_item_with_infinite_features():
     shape = dict(B=1, N=1, D=48, H=40, W=4, C=80, X=3, Y=1, Z=1)
     data = draw_small(np.random.default_rng(8), shape)
     coor = _alternate_coor(shape)
+    shape = _roomy(shape)
     data["depth"] = np.abs(data["depth"]) + np.float32(0.01)
     data["feat"][0, 0, 21, 1, 3] = np.inf
     data["depth"][0, 0, 9, 21, 1] = 0.0
@@ -175,6 +187,7 @@ def test_dense_repeated_pixels_stay_fast():
     data = draw_small(np.random.default_rng(3), dict(shape, D=1), softmax=False)
     plan = _gpu.run_prepare(random_coor(np.random.default_rng(3), shape, spread=1), shape)
     sched = bp.schedule(plan)
+    assert _dense(sched, False)
     depth = torch.rand((1, 6, 118, 40, 100), device=_gpu.DEV)
     feat = _gpu.to_dev(data["feat"])
     assert _fastest(lambda: bp.forward_scheduled(depth, feat, sched)) < 3 * _fastest(lambda: bp.forward(depth, feat, plan))
@@ -218,8 +231,9 @@ def test_dense_infinite_features_in_every_layout(C, dtype, out_dtype, logits):
     coor.reshape(2, 48, 23, 13, 3)[0, 8:, 5, 4] = -1
     for h, w, c, x in [(5, 4, 0, np.inf), (11, 0, C - 1, -np.inf), (22, 12, C // 2, np.nan), (0, 7, 17, np.inf)]:
         data["feat"][0, 0, h, w, c] = x
+    shape = _roomy(shape)
     sched = bp.schedule(_gpu.run_prepare(coor, shape))
-    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    assert _dense(sched, dtype == "f16")
     forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
                     else (bp.forward_scheduled, oracle.forward_ref))
     out = forward(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched, out_dtype=_gpu.torch_dtype(out_dtype))
@@ -238,7 +252,7 @@ def test_dense_infinite_features_stay_fast():
     and channel: 38)."""
     shape = dict(B=1, N=6, D=118, H=40, W=100, C=80, X=40, Y=8, Z=1)
     sched = bp.schedule(_gpu.run_prepare(_column_coor(shape, 4), shape))
-    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    assert _dense(sched, False)
     depth = torch.rand((1, 6, 118, 40, 100), device=_gpu.DEV)
     feat = torch.randn((1, 6, 40, 100, 80), device=_gpu.DEV)
     finite = _fastest(lambda: bp.forward_scheduled(depth, feat, sched))
@@ -251,7 +265,7 @@ def _leave_in_lds(value):
     """Fills every compute unit's staged rows and weights with `value`."""
     shape = dict(B=1, N=6, D=40, H=40, W=100, C=64, X=4, Y=4, Z=1)
     sched = bp.schedule(_gpu.run_prepare(_column_coor(shape, 10), shape))
-    assert sched.plan.n_valid >= MIN_POINTS * (sched.plan.n_intervals + sched.n_slots)
+    assert _dense(sched, False)
     bp.forward_scheduled(torch.full((1, 6, 40, 40, 100), value, device=_gpu.DEV),
                          torch.full((1, 6, 40, 100, 64), value, device=_gpu.DEV), sched)
 
@@ -265,6 +279,7 @@ def test_dense_bits_do_not_depend_on_what_lds_held(H, W, C, dtype, out_dtype):
     shape = dict(B=1, N=2, D=48, H=H, W=W, C=C, X=9, Y=3, Z=1)
     data = draw_small(np.random.default_rng(C), shape, dtype=dtype, out_dtype=out_dtype)
     coor = _column_coor(shape, 6)
+    shape = _roomy(shape)
     outs = []
     for value in (0.0, float("nan"), float("inf")):
         _leave_in_lds(value)
@@ -291,3 +306,70 @@ def test_dense_zero_weight_of_an_infinite_feature():
     nan = np.isnan(ref)
     assert nan.any() and np.array_equal(np.isnan(out), nan)
     _gpu.assert_within(out[~nan], ref[~nan], mag[~nan], "f32", "finite elements")
+
+
+def _cells_coor(shape, rows, run):
+    """Runs of `run` bins and bands of `rows` image rows, shifted from column to
+    column, each a cell of its own: strips of many segments of few pixels."""
+    B, N, D, H, W, X, Y = (shape[k] for k in "BNDHWXY")
+    b, n, d, h, w = np.indices((B, N, D, H, W))
+    bands, runs = -(-H // rows), -(-D // run)
+    cell = ((n * W + w) * bands + (h + 2 * w) % H // rows) * runs + d // run
+    assert cell.max() < X * Y
+    return np.stack([cell % X, cell // X, 0 * cell], axis=-1).reshape(-1, 3).astype(np.int32)
+
+
+def _tiles_and_rounds(sched, shape, dtype, logits):
+    """Most tiles of 16 segments that an item takes at once, and most rounds of the
+    index table."""
+    n = sched.plan.n_valid
+    got = _sched.decode(sched.buffer.cpu().numpy(), shape, n, sched.plan.n_intervals)
+    segs = int(np.diff(got["item_seg0"]).max())
+    table = _sched.dense_table(shape, n, dtype == "f16", logits, got["n"]["shares"])
+    return -(-min(segs, table) // 16), -(-segs // table)
+
+
+def _check_many_segments(shape, coor, dtype, out_dtype, logits, tiles, rounds):
+    data = draw_small(np.random.default_rng(shape["C"]), shape, dtype=dtype, out_dtype=out_dtype, softmax=not logits)
+    # infinite and NaN features at both ends of a strip and inside it
+    for h, w, c, x in [(0, 0, 1, np.inf), (shape["H"] - 1, 1, shape["C"] - 1, np.nan), (17, 2, 9, -np.inf)]:
+        data["feat"][0, 0, h, w, c] = x
+    if not logits:
+        data["depth"] = np.abs(data["depth"]) + np.asarray(0.01, dtype=data["depth"].dtype)
+    sched = bp.schedule(_gpu.run_prepare(coor, shape))
+    assert _dense(sched, dtype == "f16")
+    got = _tiles_and_rounds(sched, shape, dtype, logits)
+    assert got[0] >= tiles and got[1] >= rounds, got
+    forward, ref = ((bp.forward_scheduled_softmax, oracle.forward_softmax_ref) if logits
+                    else (bp.forward_scheduled, oracle.forward_ref))
+    out = forward(_gpu.to_dev(data["depth"]), _gpu.to_dev(data["feat"]), sched, out_dtype=_gpu.torch_dtype(out_dtype))
+    out = out.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        want, mag = ref(data["depth"], data["feat"], coor, shape)
+    fine = np.isfinite(want)
+    assert (~fine).sum() > 8
+    assert np.array_equal(out[~fine].astype(np.float64), want[~fine], equal_nan=True)
+    _gpu.assert_within(out[fine], want[fine], mag[fine], dtype, f"{shape} {dtype} {out_dtype}")
+
+
+# three tiles and more, in one pass of channels and in several, of 2 to 5 channel tiles
+@pytest.mark.parametrize("C", [40, 52, 80, 96, 128, 264, 520])
+@pytest.mark.parametrize("dtype,out_dtype", [("f32", "f32"), ("f16", "f16"), ("f16", "f32")])
+@pytest.mark.parametrize("logits", [False, True])
+def test_dense_many_tiles(C, dtype, out_dtype, logits):
+    if dtype == "f16" and C % 8:
+        C += 4
+    shape = dict(B=1, N=2, D=48, H=41, W=4, C=C, X=432, Y=2, Z=1)
+    _check_many_segments(shape, _cells_coor(shape, 5, 8), dtype, out_dtype, logits, tiles=3, rounds=1)
+
+
+# items of more segments than the index table holds: the table again and again, with
+# the strips too many for the large one (a table of 48 to 112), and with few strips
+@pytest.mark.parametrize("B,N,W,D,run,C,dtype,out_dtype", [(4, 8, 45, 16, 4, 36, "f32", "f32"), (4, 8, 45, 24, 6, 64, "f32", "f32"),
+                                                           (4, 8, 45, 18, 5, 40, "f16", "f16"), (4, 8, 45, 18, 5, 40, "f16", "f32"),
+                                                           (1, 2, 4, 48, 8, 40, "f32", "f32"), (1, 2, 4, 48, 8, 40, "f16", "f32")])
+@pytest.mark.parametrize("logits", [False, True])
+def test_dense_rounds_of_the_index_table(B, N, W, D, run, C, dtype, out_dtype, logits):
+    shape = dict(B=B, N=N, D=D, H=40 if B > 1 else 41, W=W, C=C, X=160, Y=72 if B > 1 else 3, Z=1)
+    rows = 8 if C == 36 else 5
+    _check_many_segments(shape, _cells_coor(shape, rows, run), dtype, out_dtype, logits, tiles=3, rounds=2)
