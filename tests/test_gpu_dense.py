@@ -373,3 +373,21 @@ def test_dense_rounds_of_the_index_table(B, N, W, D, run, C, dtype, out_dtype, l
     shape = dict(B=B, N=N, D=D, H=40 if B > 1 else 41, W=W, C=C, X=160, Y=72 if B > 1 else 3, Z=1)
     rows = 8 if C == 36 else 5
     _check_many_segments(shape, _cells_coor(shape, rows, run), dtype, out_dtype, logits, tiles=3, rounds=2)
+
+
+@pytest.mark.parametrize("dtype,unit", [("f32", 2.0 ** -149), ("f16", 2.0 ** -24)])
+@pytest.mark.parametrize("tiny", ["feat", "depth"])
+def test_dense_keeps_subnormal_operands(dtype, unit, tiny):
+    """Whole multiples of the smallest subnormal: sums below 2^23 of it, exact in any
+    order."""
+    shape = dict(B=1, N=1, D=12, H=40, W=4, C=80, X=12, Y=4, Z=1)
+    coor = _column_coor(shape, 3)
+    rng = np.random.default_rng(9)
+    np_type = np.float16 if dtype == "f16" else np.float32
+    whole = dict(depth=rng.integers(1, 4, (1, 1, 12, 40, 4)), feat=rng.integers(-100, 100, (1, 1, 40, 4, 80)))
+    data = {k: (v * (unit if k == tiny else 1.0)).astype(np_type) for k, v in whole.items()}
+    out, dense, _ = _forward(coor, data, shape, "f32")
+    assert dense, "the case is meant for the matrix cores"
+    ref, _ = oracle.forward_ref(whole["depth"].astype(np.float64), whole["feat"].astype(np.float64), coor, shape)
+    assert np.abs(ref).max() < 2 ** 23 and np.abs(ref).max() > 0
+    assert np.array_equal(out.astype(np.float64) / unit, ref)
