@@ -143,9 +143,9 @@ struct Reduce {
 
 // VEC elements of a row in the registers they were loaded to; float16 ones stay
 // so until a multiply-add takes them (one instruction converts and multiplies).
-// The first LEAD are one 16-byte vector of the features and the others a tail: the
-// vectors of a row's lanes lie side by side, and after them the tails, so that each
-// load touches whole cache lines.
+// The first LEAD are one vector of at most 16 bytes and the others a tail: the vectors
+// of a row's lanes lie side by side, and after them the tails, so that each load
+// touches whole cache lines.
 constexpr int row_lead(int elem, int vec) { return vec * elem > 16 ? 16 / elem : vec; }
 template <typename T, int VEC, int LEAD>
 struct RowReg {
@@ -252,8 +252,14 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
   const int CV = C / VEC;
   const __amdgpu_buffer_rsrc_t rows = buffer_of(grad_out, WIDE ? 0 : (int32_t)(a.cells * C * (int64_t)sizeof(TG)));
 
-  // this lane's channels: kLead from v kLead on and kTails from CV kLead + v kTails on
-  constexpr int kLead = row_lead((int)sizeof(TIn), VEC), kTails = VEC - kLead;
+  // this lane's channels: kLead from v kLead on and kTails from CV kLead + v kTails on.
+  // (In rows of several parts the wider type's 16 bytes: with float16's 8 channels a
+  // lane's float32 gradients are two vectors side by side, and each load touches all
+  // the lines of both.  1,024 channels, float16 with float32 gradients, from a schedule:
+  // 297 -> 243 us at 640x1600, 86 -> 68 us for two samples at 256x704.  Rows of one part
+  // take the same time either way.)
+  constexpr int kElem = (int)(NV > 1 && sizeof(TG) > sizeof(TIn) ? sizeof(TG) : sizeof(TIn));
+  constexpr int kLead = row_lead(kElem, VEC), kTails = VEC - kLead;
   typedef RowReg<TIn, VEC, kLead> InRow;
   typedef RowReg<TG, VEC, kLead> GRow;
   InRow fv[NV];
@@ -432,7 +438,7 @@ __attribute__((amdgpu_waves_per_eu(UMAX == 4 && NV == 1 ? 5 : 1))) void k_bwd_pi
     TIn* const p = grad_feat + f * C;
     Vec<TIn, kLead>::store(p + v * kLead, acc[k]);
     TIn* const t = p + CV * kLead + v * kTails;
-    if constexpr (kTails == 4 && sizeof(TIn) == 4) {
+    if constexpr (kTails == 4) {
       Vec<TIn, 4>::store(t, acc[k] + kLead);
     } else if constexpr (kTails > 0) {
 #pragma unroll

@@ -99,14 +99,7 @@ __device__ __forceinline__ void store_sums(float* p, const float* v) {
 }
 template <int N>
 __device__ __forceinline__ void store_sums(half_t* p, const float* v) {
-  if constexpr (N == 8) {
-    Vec<half_t, 8>::store(p, v);
-  } else {
-    half4_t t;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = (half_t)v[e];
-    *reinterpret_cast<half4_t*>(p) = t;
-  }
+  Vec<half_t, N>::store(p, v);
 }
 
 // An item with a pixel that meets a segment again, whose pairs are walked: lane

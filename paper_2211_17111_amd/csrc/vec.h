@@ -61,6 +61,17 @@ struct Vec<half_t, 8> {
   }
 };
 
+// (half of a row's vector of 8, where its float32 gradient takes 4 to a load)
+template <>
+struct Vec<half_t, 4> {
+  __device__ static __forceinline__ void store(half_t* p, const float* v) {
+    half4_t t;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = (half_t)v[e];
+    *reinterpret_cast<half4_t*>(p) = t;
+  }
+};
+
 // float32 output of float16 inputs: 8 floats = two 16-byte stores.
 template <>
 struct Vec<float, 8> {

@@ -94,6 +94,15 @@ def test_narrow_rows(C, dtype, out_dtype, B, H, W, D, path):
     test_channel_layouts(C, dtype, out_dtype, B, H, W, D, path)
 
 
+# rows of two parts, the second of one lane up to all of them; few pixels and many
+@pytest.mark.parametrize("C", [520, 768, 1024])
+@pytest.mark.parametrize("dtype,out_dtype", [("f32", "f32"), ("f16", "f16"), ("f16", "f32")])
+@pytest.mark.parametrize("B,H,W,D", [(1, 3, 7, 20), (1, 41, 55, 3)])
+@pytest.mark.parametrize("path", ["plan", "scheduled"])
+def test_rows_of_two_parts(C, dtype, out_dtype, B, H, W, D, path):
+    test_channel_layouts(C, dtype, out_dtype, B, H, W, D, path)
+
+
 @pytest.mark.parametrize("path", ["plan", "scheduled"])
 def test_gradient_of_a_gibibyte(path):
     """grad_out of 1 GiB: its rows lie beyond what the 32-bit offsets address."""
