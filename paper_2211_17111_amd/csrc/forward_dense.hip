@@ -17,18 +17,19 @@
 //      covers its cell, else into its slot.  k_fwd_combine then adds the slots.
 //
 // A table entry without a pair adds +-0 for a finite feature.  Where a sum
-// comes out infinite or NaN its segment is summed again from its pairs alone,
-// so an infinite feature reaches only the cells whose points see it.  The
-// order of a sum depends only on the schedule: results are bitwise
-// reproducible.
+// comes out infinite or NaN it is formed again from its segment's own pixels, so
+// an infinite feature reaches only the cells whose points see it.  An item in
+// which a pixel meets a segment twice walks its pairs instead (walk_item).  The
+// order of a sum depends only on the schedule: results are bitwise reproducible.
 //
 // What bounds it: the chain item header -> pair records -> depth gathers ->
 // products of each workgroup, about 12 us at 640x1600, where all 715 items are
 // resident at once (three workgroups of 8 waves to a CU, by LDS and at most 80
-// VGPRs); with many items (four frames) the issue of vector instructions, about
-// 50 per pair, and 13 us of matrix time.  k_fwd_strips against this kernel,
-// kernel time: 640x1600 float32 25.5 -> 22.2 us, from logits 32.8 -> 22.1 us;
-// four frames at 640x1760, float16, 116 -> 67 us.
+// VGPRs); with many items (four frames at 640x1760, 6.4 M pairs) the issue of
+// vector instructions, 2.4 a pair and wave, 25 us on each SIMD, and 13 us of
+// matrix time.  k_fwd_strips against this kernel, kernel time: 640x1600 float32
+// 25.5 -> 21.5 us, from logits 32.8 -> 21.8 us; the four frames in float16 116 ->
+// 76 us.
 
 #include "device_utils.h"
 #include "internal.h"

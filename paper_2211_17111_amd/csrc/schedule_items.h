@@ -9,9 +9,9 @@
 
 namespace bevpool {
 
-// floor(n / d) for 0 <= n < 2^42 and 0 < d < 2^31, quotient below 2^31.  The
-// float64 quotient is off by at most n / d 2^-53 <= 2^-11 / d and the next integer
-// above an inexact one is at least 1 / d away.  (The 64-bit integer division of
+// floor(n / d) for 0 <= n < 2^53 and 0 < d < 2^31, quotient below 2^31.  The
+// float64 quotient is off by at most n / d 2^-53 < 1 / d, and the next integer above
+// an inexact one is at least 1 / d away.  (The 64-bit integer division of
 // the compiler is a hundred instructions, and the few threads that cut strips
 // into items run a chain of them.)
 __device__ __forceinline__ int32_t div_floor(int64_t n, int64_t d) {
