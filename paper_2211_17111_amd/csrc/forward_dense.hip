@@ -54,8 +54,9 @@ constexpr int kMaxRank = 254;        // most pixels of a strip: pairs of a segme
 constexpr int kWalkGroups = kDW * 8; // most lane groups of a walk
 constexpr int kWalkStep = 4;         // pairs of a group in flight
 constexpr int kMinPoints = 18;       // points per segment from which the products pay
-constexpr double kFinePoints = 4;    // points per expected pair from which bins are fine
-constexpr double kMinFill = 0.16;    // share of the table's entries with a pair from which products pay there
+constexpr double kMinFill = 0.16;    // and share of the table's entries with a pair
+constexpr double kMinFillNarrow = 0.1;  // (float16 rows of at most kNarrowC channels)
+constexpr int kNarrowC = 56;
 // LDS of a workgroup (less the kernel's own and the allocation's granule):
 // three to a CU; two where the items are too few to need the third
 constexpr int kDenseLds = 160 * 1024 / 3 - 2304;
@@ -662,18 +663,22 @@ hipError_t run_tiles(const Dims& d, const DenseArgs& s, int mt, size_t lds, cons
 // (voxels) 74.4 / 74.3 us.
 //
 // The products' cost goes with the table's entries, of which only those with a
-// pair do any good, and where bins are finer than cells a segment of many points
-// has few pairs.  The pairs are not known here; but a ray meets about a third of X
-// + Y cells (0.34 of them at 4x100 pixels and 944 bins, 0.16 at 640x1600, where the
-// grid's height cuts the rays off), so a pixel is taken to have no more pairs.  Walk
-// against products, 80 channels in float32, at points per expected pair and
-// share of the entries: 9.7 and 0.05 (four samples at 2x100 pixels, 944 bins, 128 x 128
-// cells) 39 / 81 us; 19 and 0.15 (4x100, 64 x 64 cells) 45 / 77 us; 19 and 0.04
-// (1x100) 22 / 29 us; 9.7 and 0.14 (one sample at 4x100, 472 bins) 15.7 / 17.8 us.
-// But 5.4 and 0.66 (40x100, 472 bins) 52 / 48 us; 5.7 and 0.25 (16x44) 18.5 / 16.5
-// us; 4.8 and 0.22 (eight samples at 4x352, 128 x 128 cells) 193 / 170 us, and
-// 213 / 113 us in float16.  Between them the types differ: 9.7 and 0.13 (2x352, 944
-// bins) 143 / 174 us, and 147 / 119 us in float16, which the rule gives up.
+// pair do any good.  Where images are low, grids fine for the strip, or bins finer
+// than cells, a segment of many points has few pairs.  The pairs are not known here;
+// but a ray meets about a third of X + Y cells, so a pixel is taken to have no more
+// (0.5 to 1.05 of min(points, that) over 1,200 schedules of 59 to 944 bins, 2 to 44
+// rows and 40 to 256 channels), and the schedule walks where they fill less than 0.16
+// of the entries.  Walk against products at that share, 80 channels in float32:
+// 0.05 (four samples at 2x100 pixels, 944 bins, 128 x 128 cells) 39 / 81 us; 0.08
+// (one sample at 4x100, 236 bins) 18 / 26 us; 0.14 (two at 23x61, 77 bins, 111 x 111
+// cells, 52 channels) 19.7 / 23.5 us; but 0.25 (16x44, 472 bins) 18.5 / 16.5 us; 0.66 (40x100, 472 bins) 52 /
+// 48 us.  The walk of float16 rows of fewer than 8 vectors, with more lane groups to
+// a wave, costs more, and the line lies at 0.1: 40 channels and 0.12 (4x100, 59
+// bins, 32 x 32 cells) 28 / 16 us; at 8 vectors (64 channels) and 0.12 (472 bins, 64
+// x 64) 16.5 / 18.4 us.  Over those schedules in both types the products cost more
+// than 1.1 times the walk in 89 of 2,386 calls (at most 1.53 times, 12 bins to a
+// pair), and the walk that much more than the products in 30 that had 18 points a
+// segment (1.24).
 //
 // The index numbers a segment's pairs in a byte, so strips have at most
 // kMaxRank pixels (narrower strips than those of 32 channels and fewer).  A
@@ -683,8 +688,9 @@ bool dense_forward_ok(const Dims& d, const StripDims& sd, bool half_in, int32_t 
   const int64_t elem = half_in ? 2 : 4;
   const int64_t view_bytes = d.D * d.hw * elem, strip_bytes = (sd.bh + 1) * d.W * d.C * elem;
   const int64_t segs = (int64_t)n_intervals + n_slots;
-  const double pairs = (double)(d.X + d.Y) / 3 * (double)d.rows;  // most that are expected
-  const bool sparse = n_valid > kFinePoints * pairs && pairs < kMinFill * (double)segs * (double)sd.pixels;
+  const double pairs = std::min((double)n_valid, (double)(d.X + d.Y) / 3 * (double)d.rows);  // most that are expected
+  const double fill = half_in && d.C <= kNarrowC ? kMinFillNarrow : kMinFill;
+  const bool sparse = pairs < fill * (double)segs * (double)sd.pixels;
   return !sparse && sd.pixels <= kMaxRank && view_bytes < ((int64_t)1 << 31) && strip_bytes < ((int64_t)1 << 31) &&
          n_valid >= kMinPoints * segs;
 }

@@ -25,6 +25,10 @@ def _shape(B, H, W, D, X, C, N=6, Z=1):
     ((4, 4, 100, 944, 64, 80), (7928376, 15799, 12145), False),
     ((4, 1, 100, 944, 64, 80), (1982094, 15799, 7355), False),
     ((1, 4, 100, 472, 64, 64), (991752, 3948, 3096), False),
+    # low images, grids fine for their strips
+    ((1, 4, 100, 236, 128, 80), (496348, 15694, 8032), False),
+    ((4, 8, 44, 236, 128, 80), (1348230, 52513, 21311), False),
+    ((1, 2, 352, 118, 64, 80), (437648, 3940, 4283), True),
 ])
 @pytest.mark.parametrize("half", [False, True])
 def test_rule_at_counts_of_real_rigs(size, counts, dense, half):
@@ -35,3 +39,11 @@ def test_rule_needs_strips_that_a_byte_numbers():
     counts = (400000, 5000, 5000)
     assert dense_forward(_shape(1, 16, 44, 118, 128, 36), *counts)       # 224 pixels
     assert not dense_forward(_shape(1, 16, 44, 118, 128, 32), *counts)   # 256
+
+
+def test_rule_of_narrow_float16_rows():
+    """Their walk costs more, so emptier tables pay."""
+    counts = (124840, 989, 1031)
+    assert dense_forward(_shape(1, 4, 100, 59, 32, 40), *counts, half=True)
+    assert not dense_forward(_shape(1, 4, 100, 59, 32, 40), *counts)
+    assert not dense_forward(_shape(1, 4, 100, 472, 64, 64), 991752, 3948, 3096, half=True)

@@ -126,7 +126,7 @@ def _alternate_coor(shape):
 @pytest.mark.parametrize("C,dtype,out_dtype", [(40, "f32", "f32"), (52, "f32", "f32"), (80, "f16", "f32"),
                                                (128, "f16", "f16"), (256, "f32", "f32"), (260, "f32", "f32"),
                                                (264, "f16", "f16"), (520, "f16", "f32")])
-@pytest.mark.parametrize("X,Y,D,H,W", [(2, 1, 64, 9, 11), (3, 1, 41, 40, 5), (5, 3, 75, 8, 33), (9, 7, 128, 3, 16)])
+@pytest.mark.parametrize("X,Y,D,H,W", [(2, 1, 64, 9, 11), (3, 1, 65, 40, 5), (5, 3, 75, 8, 33), (9, 7, 128, 3, 16)])
 @pytest.mark.parametrize("logits", [False, True])
 def test_dense_walked_items(X, Y, D, H, W, C, dtype, out_dtype, logits):
     shape = dict(B=1, N=2, D=D, H=H, W=W, C=C, X=X, Y=Y, Z=1)
