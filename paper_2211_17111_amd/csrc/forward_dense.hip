@@ -671,14 +671,14 @@ hipError_t run_tiles(const Dims& d, const DenseArgs& s, int mt, size_t lds, cons
 // of the entries.  Walk against products at that share, 80 channels in float32:
 // 0.05 (four samples at 2x100 pixels, 944 bins, 128 x 128 cells) 39 / 81 us; 0.08
 // (one sample at 4x100, 236 bins) 18 / 26 us; 0.14 (two at 23x61, 77 bins, 111 x 111
-// cells, 52 channels) 19.7 / 23.5 us; but 0.25 (16x44, 472 bins) 18.5 / 16.5 us; 0.66 (40x100, 472 bins) 52 /
-// 48 us.  The walk of float16 rows of fewer than 8 vectors, with more lane groups to
-// a wave, costs more, and the line lies at 0.1: 40 channels and 0.12 (4x100, 59
-// bins, 32 x 32 cells) 28 / 16 us; at 8 vectors (64 channels) and 0.12 (472 bins, 64
-// x 64) 16.5 / 18.4 us.  Over those schedules in both types the products cost more
-// than 1.1 times the walk in 89 of 2,386 calls (at most 1.53 times, 12 bins to a
-// pair), and the walk that much more than the products in 30 that had 18 points a
-// segment (1.24).
+// cells, 52 channels) 19.7 / 23.5 us; but 0.25 (16x44, 472 bins) 18.5 / 16.5 us;
+// 0.66 (40x100, 472 bins) 52 / 48 us.  The walk of float16 rows of fewer than 8
+// vectors, with more lane groups to a wave, costs more, and the line lies at 0.1: 40
+// channels and 0.12 (4x100, 59 bins, 32 x 32 cells) 28 / 16 us; at 8 vectors (64
+// channels) and 0.12 (472 bins, 64 x 64) 16.5 / 18.4 us.  Over those schedules in
+// both types the products cost more than 1.1 times the walk in 89 of 2,386 calls (at
+// most 1.53 times, 12 bins to a pair), and the walk that much more than the products
+// in 30 that had 18 points a segment (1.24).
 //
 // The index numbers a segment's pairs in a byte, so strips have at most
 // kMaxRank pixels (narrower strips than those of 32 channels and fewer).  A
